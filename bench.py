@@ -97,9 +97,11 @@ def kernel_source_hash():
     """Hash of the LM-head kernel code (comments excluded, so counters stay
     attached to the code they were taken on when only comments change)."""
     h = hashlib.sha256()
-    for f in ("lmhead.hip", "common.h"):
-        with open(os.path.join(ROOT, "paper_2606_08411_amd", "csrc", f)) as fh:
-            h.update(_code_only(fh.read()).encode())
+    for f in ("lmhead.hip", "lmhead.h", "lmhead_tile.h", "common.h"):
+        path = os.path.join(ROOT, "paper_2606_08411_amd", "csrc", f)
+        if os.path.exists(path):
+            with open(path) as fh:
+                h.update(_code_only(fh.read()).encode())
     return h.hexdigest()[:16]
 
 

@@ -14,7 +14,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libasynclane.so")
-SOURCES = ["abi.cpp", "scheduler.cpp", "lmhead.hip", "lane_attn.hip", "select_unmask.hip"]
+SOURCES = (["abi.cpp", "scheduler.cpp", "lane_attn.hip", "lmhead.hip", "select_unmask.hip"] +
+           [f"lmhead_tile_{g}.hip" for g in "abcdefghi"])
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -40,7 +41,7 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(BUILD, os.path.splitext(s)[0] + ".o")
         objs.append(obj)
         cmds.append([HIPCC, "-x", "hip", "-c", os.path.join(CSRC, s), "-o", obj] + FLAGS)
-    with ThreadPoolExecutor(len(cmds)) as ex:
+    with ThreadPoolExecutor(min(len(cmds), 8)) as ex:
         for err in ex.map(_run, cmds):
             if verbose and err.strip():
                 print(err, file=sys.stderr)

@@ -1,0 +1,77 @@
+// Shared by the LM-head kernels.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include "common.h"
+
+namespace al {
+
+constexpr float LM_LOG2E = 1.4426950408889634f;
+
+struct LmPartial {
+  float m;
+  float s;
+  int idx;
+  int pad;
+};
+
+// Merge (m2, s2, i2) into (m, s, i): max, rescaled sum, lowest index on ties.
+// Commutative, so lanes that exchange states obtain identical bits.
+__device__ __forceinline__ void merge_state(float& m, float& s, int& idx, float m2, float s2,
+                                            int idx2) {
+  if (m2 == -INFINITY) return;
+  if (m == -INFINITY) {
+    m = m2;
+    s = s2;
+    idx = idx2;
+    return;
+  }
+  const float M = fmaxf(m, m2);
+  s = s * exp2_fast((m - M) * LM_LOG2E) + s2 * exp2_fast((m2 - M) * LM_LOG2E);
+  if (m2 > m || (m2 == m && idx2 < idx)) idx = idx2;
+  m = M;
+}
+
+template <int N>
+struct IntTag {
+  static constexpr int value = N;
+};
+
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(IntTag<I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+struct LmTileParams {
+  const uint16_t* hidden;
+  const int32_t* row_idx;
+  const uint16_t* W;
+  const uint8_t* sup;
+  LmPartial* part;  // [n_nt][COLS][n_vt]
+  int N, d, V, eos_id;
+  int n_hg, n_vt, n_nt, tiles_total, tiles_per_xcd;
+};
+
+// The instances built, X(RA, CBT): 64 RA vocabulary rows x 16 CBT columns.
+// Their products must fit a wavefront's 256 registers at two wavefronts per
+// SIMD (RA CBT <= 65 beside the two sets of fragments); RA = 8 serves very
+// large vocabularies.  The sources lmhead_tile_*.hip hold a few each.
+#define AL_LM_INSTANCES(X)                                                                  \
+  X(1, 2) X(1, 4) X(1, 6) X(1, 8) X(1, 10) X(1, 13) X(1, 16)                                \
+  X(2, 2) X(2, 4) X(2, 6) X(2, 8) X(2, 10) X(2, 13) X(2, 16)                                \
+  X(4, 2) X(4, 4) X(4, 6) X(4, 8) X(4, 9) X(4, 10) X(4, 11) X(4, 12) X(4, 13) X(4, 14)      \
+  X(4, 15) X(4, 16)                                                                         \
+  X(5, 4) X(5, 6) X(5, 8) X(5, 9) X(5, 10) X(5, 11) X(5, 12) X(5, 13)                       \
+  X(8, 2) X(8, 4) X(8, 6)
+
+// Launch one instance (nt: W loaded non-temporally).
+template <int RA, int CBT>
+void launch_lmhead_tile(const LmTileParams& p, bool packed, bool nt, dim3 grid, hipStream_t stream);
+
+}  // namespace al

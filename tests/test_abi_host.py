@@ -206,3 +206,11 @@ def test_lmhead_packed_validation(lib):
     assert f(None, 10, None, 5, FAKE, 64, 100, None, -1, FAKE, FAKE, None, FAKE, 1 << 30, None) == -1
     assert f(FAKE, 10, None, 5, FAKE, 64, 100, None, -1, FAKE, FAKE, None, FAKE, 16, None) == -4
     assert f(FAKE, 10, None, 0, FAKE, 64, 100, None, -1, None, None, None, None, 0, None) == 0
+
+
+def test_lmhead_workspace_serves_smaller_calls(lib):
+    """A workspace made for N rows is large enough for every smaller N (a
+    decode loop allocates once for its largest step)."""
+    for V in (1, 33, 1024, 9000, 32000, 126464, 152064, 300001, 1 << 24):
+        sizes = [lib.lmhead_confidence_workspace_size(n, 4096, V) for n in range(1, 1300)]
+        assert all(b >= a > 0 for a, b in zip(sizes, sizes[1:])), V
