@@ -83,4 +83,52 @@ __device__ __forceinline__ float pair_sum32(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+template <int N>
+struct IntTag {
+  static constexpr int value = N;
+};
+
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(IntTag<I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// 16 zero bytes in device memory: the source of padding loaded to LDS.
+static __device__ __attribute__((aligned(16))) const unsigned char zero_seg16[16] = {};
+
+// Direct global->LDS loads of 16 bytes per lane: lane l's bytes land at
+// lds + 16 l.  Inline asm, because the compiler waits for every outstanding
+// load before any LDS read that follows the builtin; the waits are the
+// kernel's own (wait_loads_and_barrier).  No register is written.
+// LDS address lds + LOFF + OFF, global address sbase + voff + OFF.
+template <int LOFF, int OFF, bool NT>
+__device__ __forceinline__ void load_to_lds16(const char* sbase, unsigned voff, unsigned lds) {
+  if (NT)
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4 nt"
+                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4"
+                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc");
+}
+// The same with a 64-bit address per lane; LDS address lds + LOFF.
+template <int LOFF>
+__device__ __forceinline__ void load_to_lds16(const char* vaddr, unsigned lds) {
+  asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               ::"s"(lds), "v"(vaddr), "n"(LOFF) : "memory", "scc");
+}
+
+__device__ __forceinline__ const char* uniform_ptr(const char* q) {
+  const unsigned long long v = (unsigned long long)q;
+  return (const char*)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) |
+                       (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v));
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 }  // namespace al

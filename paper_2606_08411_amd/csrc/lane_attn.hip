@@ -7,12 +7,12 @@
 // tree and, bidirectionally, its own block.
 //
 // Kernel layout.  A workgroup of 8 wavefronts serves one K/V head and eight
-// query tiles (32 query rows of one lane and one query head each; for
-// grouped-query attention the Hq/Hkv heads of a lane are adjacent tiles).
-// Key tiles of 64 rows are staged once per workgroup in LDS, K and V both
-// row-major as loaded, and consumed by every wavefront whose lane sees them,
-// so a prefix tile read from HBM serves all lanes of the workgroup.  Both
-// products run transposed on the 32x32x16 bf16 MFMA:
+// (or four) query tiles (32 query rows of one lane and one query head each;
+// for grouped-query attention the Hq/Hkv heads of a lane are adjacent tiles).
+// Key tiles of 64 rows reach LDS once per workgroup by direct loads, K and V
+// both row-major with their 16-byte segments permuted, and are consumed by
+// every wavefront whose lane sees them, so a prefix tile read from HBM serves
+// all lanes of the workgroup.  Both products run transposed on the 32x32x16 bf16 MFMA:
 //     S^T = K Q^T      (lane l owns query row l%32, half of the keys)
 //     O^T = V^T P^T    (lane l owns query row l%32, a quarter of D)
 // so the running max / sum of the online softmax and the rescale of O stay
@@ -64,18 +64,31 @@ struct AttnParams {
   int P, Hq, Hkv, g;
   int B_keys, n_key_lanes, lane_key_tiles, n_pre_tiles, total_key_tiles, n_split;
   float scale_log2;
+  int tpw;                 // query tiles (computing wavefronts) per workgroup: 8 or 4
   unsigned long long vis[AT_MAX_LANES];  // bit j: lane block j visible to lane i
 };
 
-// Two wavefronts per SIMD (<= 256 registers each, no spills at D = 128),
-// one workgroup per CU: the next tile's loads go to registers while the
-// current tile is multiplied, and the two wavefronts of a SIMD interleave
-// their MFMA and VALU phases.  At one wavefront per SIMD (312 registers)
-// the phases serialize: 530 us vs 270 us on the Wide lane pass (MI355X).
-// Eight query tiles per workgroup instead of four (two 4-wavefront
-// workgroups per CU) halve the K/V staging per MFMA: Wide lane + refresh
-// passes 293-297 us against 308-310 us per call, Long 53 us either way
-// (one box, two runs each; identical outputs).
+// Two wavefronts per SIMD (256 registers each), one workgroup per CU.
+//
+// What bounds it: a 64-key tile is 32 MFMAs (1024 cycles) and ~600 cycles of
+// vector work per wavefront, so two wavefronts per SIMD need 2048 cycles a
+// tile if vector work hides under MFMAs; it takes about 3900 (1.8 us).  Cycle
+// stamps of the layout before (registers -> LDS staging, two barriers a
+// tile, one wavefront's products and softmax in sequence) showed 4400-5000:
+// both wavefronts of a SIMD reach the softmax together, because both leave
+// each barrier together and the older one is served first.  Hence
+// * in the prefix the next tile's Q K^T stands between the steps of this
+//   tile's softmax, MFMA by MFMA, and the softmax's second half between the
+//   MFMAs of P V, so that one wavefront keeps both units busy;
+// * wavefronts 0-3 (or, with four query tiles, the idle 4-7) issue direct
+//   loads three tiles ahead; no registers or LDS stores are spent on staging;
+// * one path for full and ragged tiles (where two met, 128 accumulator
+//   registers were copied per tile), and a tile walk that costs a few scalar
+//   operations.
+// Per call, same box, graph replay, before -> after: window of 2563 rows x 32
+// heads 195 -> 153 us (D = 64 136 -> 107), 1531 rows x 28 heads on 4 K/V heads
+// 76 -> 50, 1024 rows x 32 heads 42 -> 34, Wide lane + refresh 233 -> 204, Long
+// 43.7 -> 40.
 constexpr int AT_OCC = 2;
 
 template <int D>
@@ -83,11 +96,13 @@ __global__ __launch_bounds__(AT_THREADS) __attribute__((amdgpu_waves_per_eu(AT_O
 void lane_attn_kernel(AttnParams p) {
   constexpr int KS = D / 16;       // MFMA k-steps of S^T = K Q^T
   constexpr int DT = D / 32;       // 32-row tiles of O^T
-  constexpr int KSTR = D + 8;      // bf16 per K row in LDS (+16 B: spreads banks)
-  constexpr int VROW = D + 32;     // bf16 per V row in LDS (rows 64 B apart in bank order)
-  constexpr int DSEG = D / 8;      // 16-byte segments per K/V row
-  __shared__ __attribute__((aligned(16))) uint16_t k_s[AT_KT * KSTR];
-  __shared__ __attribute__((aligned(16))) uint16_t v_s[AT_KT * VROW];
+  constexpr int ROWB = 2 * D;      // bytes of a K or V row in LDS
+  constexpr int TB = AT_KT * ROWB; // bytes of a K or V tile
+  constexpr int RPP = 1024 / ROWB; // rows per 1 KB piece (one direct load of a wavefront)
+  constexpr int AHEAD = 4;         // K fragments read ahead
+  constexpr int PW = AT_KT / RPP / 4;  // pieces per tile and loading wavefront
+  // Four tile buffers, K then V.
+  __shared__ __attribute__((aligned(1024))) char lds[8 * TB];
 
   const int hk = blockIdx.y;
   const int split = blockIdx.z;
@@ -101,8 +116,9 @@ void lane_attn_kernel(AttnParams p) {
   const int per_lane = p.tiles_per_lane * p.g;
 
   // This wavefront's query tile.
-  const int qt = blockIdx.x * AT_WAVES + w;
-  const bool active = qt < p.q_tiles_kv;
+  const int tpw = p.tpw;
+  const int qt = blockIdx.x * tpw + w;
+  const bool active = w < tpw && qt < p.q_tiles_kv;
   int lane_i = 0, c = 0, hg = 0;
   if (active) {
     lane_i = qt / per_lane;
@@ -116,15 +132,10 @@ void lane_attn_kernel(AttnParams p) {
   if (active) nrows = min(min(32, p.rows_per_lane - c * 32), p.n_rows - row0);
   const unsigned long long my_vis = (active && p.n_key_lanes) ? p.vis[lane_i] : 0ull;
   unsigned long long wg_vis = 0ull;
-  bool wg_active = false;
-  for (int ww = 0; ww < AT_WAVES; ++ww) {
-    const int qt2 = blockIdx.x * AT_WAVES + ww;
-    if (qt2 < p.q_tiles_kv) {
-      wg_active = true;
-      if (p.n_key_lanes) wg_vis |= p.vis[qt2 / per_lane];
-    }
+  for (int ww = 0; ww < tpw; ++ww) {
+    const int qt2 = blockIdx.x * tpw + ww;
+    if (qt2 < p.q_tiles_kv && p.n_key_lanes) wg_vis |= p.vis[qt2 / per_lane];
   }
-  if (!wg_active) return;  // uniform for the workgroup
 
   // Q fragments (B operand of S^T = K Q^T), kept in registers.
   bf16x8 qf[KS];
@@ -142,162 +153,154 @@ void lane_attn_kernel(AttnParams p) {
     for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  // Key tiles of this split: prefix tiles, then lane-block tiles.  Tiles no
-  // wavefront of the workgroup sees are skipped (uniformly).
-  const int kt0 = (int)((long long)split * p.total_key_tiles / p.n_split);
-  const int kt1 = (int)((long long)(split + 1) * p.total_key_tiles / p.n_split);
-  struct Tile {
-    const uint16_t* k;  // first key row of the tile, K/V head hk applied
-    const uint16_t* v;
-    int nvalid;         // valid keys (1..64); 0 = no tile
-    bool vis;           // this wavefront attends to it
+  // The workgroup's key tiles: the prefix tiles, then the tiles of the lane
+  // blocks some wavefront sees, in ascending order.  This split takes
+  // [t0, t1) of them.
+  const int n_tiles = p.n_pre_tiles + __popcll(wg_vis) * p.lane_key_tiles;
+  const int t0 = (int)((long long)split * n_tiles / p.n_split);
+  const int t1 = (int)((long long)(split + 1) * n_tiles / p.n_split);
+  // They come in runs of consecutive rows: the prefix, then each block.  A
+  // walk holds what is left of its run, so that the next tile costs a few
+  // scalar operations; the rest is done once per run.
+  struct Walk {
+    unsigned long long m;   // lanes not finished (lowest: the current one)
+    int row, left;          // next row of the run, rows left in it
+    bool pre;
   };
-  auto tile_at = [&](int kt) -> Tile {
-    Tile tl{nullptr, nullptr, 0, false};
-    for (; kt < kt1; ++kt) {
-      if (kt < p.n_pre_tiles) {
-        const int r0 = kt * AT_KT;
-        tl.k = p.k_pre + ((size_t)r0 * p.Hkv + hk) * D;
-        tl.v = p.v_pre + ((size_t)r0 * p.Hkv + hk) * D;
-        tl.nvalid = min(AT_KT, p.P - r0);
-        tl.vis = active;
-        return tl;
-      }
-      const int lt = kt - p.n_pre_tiles;
-      const int j = lt / p.lane_key_tiles;
-      const int sub = lt - j * p.lane_key_tiles;
-      if (!((wg_vis >> j) & 1ull)) continue;
-      const int r0 = j * p.B_keys + sub * AT_KT;
-      tl.k = p.k_lane + ((size_t)r0 * p.Hkv + hk) * D;
-      tl.v = p.v_lane + ((size_t)r0 * p.Hkv + hk) * D;
-      tl.nvalid = min(AT_KT, p.B_keys - sub * AT_KT);
-      tl.vis = active && ((my_vis >> j) & 1ull);
-      return tl;
-    }
-    return tl;
-  };
-  auto next_kt = [&](int kt) {  // index after the tile found from kt
-    for (; kt < kt1; ++kt) {
-      if (kt < p.n_pre_tiles) return kt + 1;
-      const int j = (kt - p.n_pre_tiles) / p.lane_key_tiles;
-      if ((wg_vis >> j) & 1ull) return kt + 1;
-    }
-    return kt1;
-  };
-
-  // Register staging of one tile: K and V as KREG 16-byte row segments
-  // each; both are stored row-major (V is transposed by the reads).
-  constexpr int KREG = (AT_KT * DSEG) / AT_THREADS;
-  static_assert(KREG * AT_THREADS == AT_KT * DSEG, "whole tiles per thread");
-  bf16x8 kr[KREG], vr[KREG];
-  auto load_tile = [&](const Tile& tl) {
-#pragma unroll
-    for (int i = 0; i < KREG; ++i) {
-      const int seg = tid + AT_THREADS * i;
-      const int krow = seg / DSEG;
-      const int ds = seg - krow * DSEG;
-      kr[i] = load_bf16x8(tl.k + (size_t)min(krow, tl.nvalid - 1) * p.Hkv * D + ds * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < KREG; ++i) {
-      const int seg = tid + AT_THREADS * i;
-      const int krow = seg / DSEG;
-      const int ds = seg - krow * DSEG;
-      vr[i] = load_bf16x8(tl.v + (size_t)min(krow, tl.nvalid - 1) * p.Hkv * D + ds * 8);
-    }
-  };
-  // Rows past nvalid are zeroed here (not right after the loads, which
-  // would stall on them); their scores are masked to -inf anyway.
-  auto store_tile = [&](int nvalid) {
-#pragma unroll
-    for (int i = 0; i < KREG; ++i) {
-      const int seg = tid + AT_THREADS * i;
-      const int krow = seg / DSEG;
-      const int ds = seg - krow * DSEG;
-      const bool ok = nvalid == AT_KT || krow < nvalid;
-      *reinterpret_cast<bf16x8*>(&k_s[krow * KSTR + ds * 8]) = ok ? kr[i] : zero_bf16x8();
-      *reinterpret_cast<bf16x8*>(&v_s[krow * VROW + ds * 8]) = ok ? vr[i] : zero_bf16x8();
-    }
-  };
-
-  // One staged tile: S^T = K Q^T, the online softmax update in log2 units,
-  // then O^T += V^T P^T.  Only ragged tiles (nvalid < 64) mask; a 32-key
-  // half with no valid key is skipped in both products.
-  //
-  // Wavefront priority: low for the two MFMA blocks, high for the softmax
-  // and for the tile staging between tiles, so the SIMD's arbiter favours
-  // the wavefront whose vector work the next MFMAs wait for while the other
-  // wavefront's MFMAs run (graph replay, one box, two runs each: Wide lane
-  // + refresh 253-254 us against 259-260 us, Long 50-51 us against 52-53;
-  // no gain on the wavefront-split kernel's shapes).
-  auto tile_compute = [&](int nvalid) {
-    const int nsub = (nvalid + 31) >> 5;  // 32-key halves holding valid keys
-    const f32x16 zero16 = {};
-    f32x16 sacc[2];
-    auto kfrag = [&](int kb, int ks) {
-      return *reinterpret_cast<const bf16x8*>(&k_s[(kb * 32 + r32) * KSTR + ks * 16 + hh * 8]);
-    };
-    __builtin_amdgcn_s_setprio(0);
-    if (nsub == 2) {
-      // Both 32-key halves: the two accumulation chains interleave, so
-      // consecutive MFMAs are independent.
-      sacc[0] = zero16;
-      sacc[1] = zero16;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 a0 = kfrag(0, ks), a1 = kfrag(1, ks);
-        sacc[0] = mfma32x32x16(a0, qf[ks], sacc[0]);
-        sacc[1] = mfma32x32x16(a1, qf[ks], sacc[1]);
-      }
+  auto walk_at = [&](int t) {
+    Walk k{wg_vis, 0, 0, t < p.n_pre_tiles};
+    if (k.pre) {
+      k.row = t * AT_KT;
+      k.left = p.P - k.row;
     } else {
-      sacc[0] = zero16;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) sacc[0] = mfma32x32x16(kfrag(0, ks), qf[ks], sacc[0]);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[1][r] = -INFINITY;
+      const int q = t - p.n_pre_tiles, n = p.n_key_lanes ? q / p.lane_key_tiles : 0;
+      for (int i = 0; i < n; ++i) k.m &= k.m - 1;
+      const int sub = (q - n * p.lane_key_tiles) * AT_KT;
+      k.row = k.m ? __builtin_ctzll(k.m) * p.B_keys + sub : 0;
+      k.left = p.B_keys - sub;
     }
+    return k;
+  };
+  auto next_run = [&](Walk& k) {
+    if (!k.pre) k.m &= k.m - 1;
+    k.pre = false;
+    k.row = k.m ? __builtin_ctzll(k.m) * p.B_keys : 0;
+    k.left = p.B_keys;
+  };
+
+  // Direct loads of a tile (wavefronts 0-3).  Row r's 16-byte segment s sits
+  // in slot s ^ f(r): f_K puts the 16 rows that one LDS cycle of the K reads
+  // serves into different banks, f_V the 4 (and 8) rows of a transpose read.
+  // Rows past the tile's valid keys are zero.
+  const int lrow = RPP * (w & 3) + lane * 16 / ROWB;   // row of this lane in piece 0
+  const int lslot = lane & (ROWB / 16 - 1);
+  const int fk = D == 128 ? lrow & 15 : (lrow >> 1) & 7;
+  const int fv = D == 128 ? (4 * (lrow & 3)) ^ (2 * ((lrow >> 2) & 1))
+                          : (4 * ((lrow >> 1) & 1)) ^ (2 * ((lrow >> 2) & 1));
+  const unsigned rowbytes = (unsigned)p.Hkv * ROWB;
+  const unsigned kvoff = lrow * rowbytes + (unsigned)((lslot ^ fk) * 16);
+  const unsigned vvoff = lrow * rowbytes + (unsigned)((lslot ^ fv) * 16);
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  const unsigned pstep = 4 * RPP * rowbytes;   // from a piece to the wavefront's next
+  const char *kp = nullptr, *vp = nullptr;     // next tile to load
+  auto set_source = [&](const Walk& k) {
+    const size_t off = (size_t)k.row * rowbytes + (size_t)hk * ROWB;
+    kp = reinterpret_cast<const char*>(k.pre ? p.k_pre : p.k_lane) + off;
+    vp = reinterpret_cast<const char*>(k.pre ? p.v_pre : p.v_lane) + off;
+  };
+  auto load_tile = [&](int nvalid, int buf) {
+    const unsigned l = lds0 + buf * 2 * TB + (w & 3) * 1024;
+    if (nvalid >= AT_KT) {
+      const char *kj = kp, *vj = vp;
+      static_for<PW>([&](auto j) {
+        constexpr int J = decltype(j)::value;
+        load_to_lds16<J * 4096, 0, false>(uniform_ptr(kj), kvoff, l);
+        load_to_lds16<TB + J * 4096, 0, false>(uniform_ptr(vj), vvoff, l);
+        kj += pstep;
+        vj += pstep;
+      });
+    } else {
+      const char* zero = reinterpret_cast<const char*>(zero_seg16);
+      static_for<PW>([&](auto j) {
+        constexpr int J = decltype(j)::value;
+        const bool ok = lrow + J * 4 * RPP < nvalid;
+        load_to_lds16<J * 4096>(ok ? kp + (size_t)J * pstep + kvoff : zero, l);
+        load_to_lds16<TB + J * 4096>(ok ? vp + (size_t)J * pstep + vvoff : zero, l);
+      });
+    }
+  };
+
+  // Lane addresses inside a tile: K fragment (row r32, segment 2 ks + hh) at
+  // ka ^ 32 ks; V^T fragment of 32-column tile dt at va ^ 64 dt.
+  const int ka = r32 * ROWB + ((hh ^ (D == 128 ? r32 & 15 : (r32 >> 1) & 7)) * 16);
+  const int vr = 4 * hh + (lg >> 2);
+  const int vx = D == 128 ? (4 * (vr & 3)) ^ (2 * ((vr >> 2) & 1))
+                          : (4 * ((vr >> 1) & 1)) ^ (2 * ((vr >> 2) & 1));
+  const int va = vr * ROWB + (((2 * (lgrp & 1) + ((lg & 3) >> 1)) ^ vx) * 16) + (lg & 1) * 8;
+
+  // A tile: S^T = K Q^T, the online softmax update in log2 units, then O^T +=
+  // V^T P^T.  Fragments are read ahead of their MFMAs (AHEAD of K, one 16-key
+  // step of V).
+  struct Scores {
+    f32x16 s[2];   // the two 32-key halves
+  };
+  auto read_k = [&](bf16x8* kf, int buf) {
+    const char* kt = lds + buf * 2 * TB;
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i)
+      kf[i] = *reinterpret_cast<const bf16x8*>(kt + (ka ^ (32 * (i >> 1))) + (i & 1) * 32 * ROWB);
+  };
+  auto qk = [&](Scores& sc, const bf16x8* kf) {
+    const f32x16 zero16 = {};
+    // The two accumulation chains interleave, so consecutive MFMAs are independent.
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i)
+      sc.s[i & 1] = mfma32x32x16(kf[i], qf[i >> 1], i < 2 ? zero16 : sc.s[i & 1]);
+  };
+  auto vfrag = [&](int buf, int ks2, int dt) {
+    const uint16_t* a = reinterpret_cast<const uint16_t*>(lds + buf * 2 * TB + TB + (va ^ (64 * dt)) + 16 * ks2 * ROWB);
+    return cat_bf16x4(lds_read_tr16(a), lds_read_tr16(a + 8 * D));
+  };
+  auto mask = [&](Scores& sc, int nvalid) {
     if (nvalid < AT_KT) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-          sacc[kb][r] = (key < nvalid) ? sacc[kb][r] : -INFINITY;
+          sc.s[kb][r] = (key < nvalid) ? sc.s[kb][r] : -INFINITY;
         }
     }
-    __builtin_amdgcn_s_setprio(1);
-    // The max is taken on the raw scores (the scale is positive, so
-    // max-then-scale is exact); each exponent is then one FMA.
-    float mx = -INFINITY;
+  };
+  // The softmax in pieces that can stand between MFMAs.  The max is taken on
+  // the raw scores (the scale is positive, so max-then-scale is exact); each
+  // exponent is then one FMA.
+  auto max_piece = [&](float mx, const Scores& sc, int q) {   // q = 0..3: 8 scores
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[kb][r]);
-    mx = pair_max32(mx);
-    const float m_tile = mx * p.scale_log2;
-    const float m_new = m_tile > m_run + AT_RESCALE_LOG2 ? m_tile : m_run;
+    for (int r = 0; r < 8; ++r) mx = fmaxf(mx, sc.s[q >> 1][8 * (q & 1) + r]);
+    return mx;
+  };
+  auto new_max = [&](float mx, float& m_new) {   // returns the factor on O
+    const float m_tile = pair_max32(mx) * p.scale_log2;
+    m_new = m_tile > m_run + AT_RESCALE_LOG2 ? m_tile : m_run;
     const float alpha = exp2_fast(m_run - m_new);
-    // P in bf16 (round-to-nearest-even, two values per conversion), packed
-    // per 16-key MFMA step; the row sum adds the rounded values (bf16 dot
-    // products with 1), so O / l is a convex combination of V rows.
-    float rs = 0.f;
-    bf16x8 pk[4];
-    const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-    for (int ks2 = 0; ks2 < 4; ++ks2)
-#pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        const int r = 8 * (ks2 & 1) + e;
-        bf16x2 pr;
-        pr[0] = (__bf16)exp2_fast(fmaf(sacc[ks2 >> 1][r], p.scale_log2, -m_new));
-        pr[1] = (__bf16)exp2_fast(fmaf(sacc[ks2 >> 1][r + 1], p.scale_log2, -m_new));
-        pk[ks2][e] = pr[0];
-        pk[ks2][e + 1] = pr[1];
-        rs = __builtin_amdgcn_fdot2_f32_bf16(pr, one2, rs, false);
-      }
-    rs = pair_sum32(rs);
-    l_run = l_run * alpha + rs;
     m_run = m_new;
+    return alpha;
+  };
+  // P in bf16 (round-to-nearest-even, two values per conversion), packed per
+  // 16-key MFMA step; the row sum adds the rounded values (bf16 dot products
+  // with 1), so O / l is a convex combination of V rows.
+  auto exp_pair = [&](const Scores& sc, bf16x8* pk, float m_new, float& rs, int q) {   // q = 0..15
+    const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
+    const int ks2 = q >> 2, e = 2 * (q & 3), r = 8 * (ks2 & 1) + e;
+    bf16x2 pr;
+    pr[0] = (__bf16)exp2_fast(fmaf(sc.s[ks2 >> 1][r], p.scale_log2, -m_new));
+    pr[1] = (__bf16)exp2_fast(fmaf(sc.s[ks2 >> 1][r + 1], p.scale_log2, -m_new));
+    pk[ks2][e] = pr[0];
+    pk[ks2][e + 1] = pr[1];
+    rs = __builtin_amdgcn_fdot2_f32_bf16(pr, one2, rs, false);
+  };
+  auto rescale = [&](float alpha) {
     // Rescale O only when some row's reference max moved (otherwise alpha
     // is exactly 1 and the product would change nothing).
     if (__builtin_amdgcn_read_exec() & __ballot(alpha != 1.0f)) {
@@ -306,57 +309,161 @@ void lane_attn_kernel(AttnParams p) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
     }
-    __builtin_amdgcn_s_setprio(0);
-    // O^T += V^T P^T, one 16-key MFMA step at a time.  The V^T fragment
-    // of lane (d, h) is keys 16 ks2 + 4h + {0..3, 8..11} at column d: two
-    // transpose reads of 4 x 16 blocks of the row-major V tile.
+  };
+  // O^T += V^T P^T, one 16-key MFMA step at a time, the second half of P's
+  // exponentials between the MFMAs of the first two steps.  The V^T fragment
+  // of lane (d, h) is keys 16 ks2 + 4h + {0..3, 8..11} at column d: two
+  // transpose reads of 4 x 16 blocks of the row-major V tile.
+  auto pv = [&](const Scores& sc, bf16x8* pk, float m_new, float alpha, float rs, int buf) {
+    bf16x8 vf[2][DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) vf[0][dt] = vfrag(buf, 0, dt);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks2 = 0; ks2 < 4; ++ks2) {
-      if ((ks2 >> 1) < nsub) {
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const uint16_t* va = &v_s[(16 * ks2 + 4 * hh + (lg >> 2)) * VROW + dt * 32 + 16 * (lgrp & 1) + 4 * (lg & 3)];
-          const bf16x8 a = cat_bf16x4(lds_read_tr16(va), lds_read_tr16(va + 8 * VROW));
-          oacc[dt] = mfma32x32x16(a, pk[ks2], oacc[dt]);
+      for (int dt = 0; dt < DT; ++dt) {
+        if (ks2 < 3) vf[(ks2 + 1) & 1][dt] = vfrag(buf, ks2 + 1, dt);
+        oacc[dt] = mfma32x32x16(vf[ks2 & 1][dt], pk[ks2], oacc[dt]);
+        if (ks2 < 2) {
+#pragma unroll
+          for (int q = 0; q < 4 / DT; ++q) exp_pair(sc, pk, m_new, rs, 8 + ks2 * 4 + dt * (4 / DT) + q);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __builtin_amdgcn_s_setprio(1);
+    l_run = l_run * alpha + pair_sum32(rs);
+  };
+  // Q K^T of the tile in buffer bq into nxt, with the max and the first half
+  // of the exponentials of cur between its MFMAs; then cur's P V.
+  auto hot_tile = [&](const Scores& cur, Scores& nxt, int bq, int bv) {
+    bf16x8 kf[2 * KS], pk[4];
+    const f32x16 zero16 = {};
+    const char* kt = lds + bq * 2 * TB;
+    auto kread = [&](int i) {
+      kf[i] = *reinterpret_cast<const bf16x8*>(kt + (ka ^ (32 * (i >> 1))) + (i & 1) * 32 * ROWB);
+    };
+    float mx = -INFINITY, m_new, alpha, rs = 0.f;
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) kread(i);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int MX = KS / 2;                 // MFMAs with a piece of the max
+    constexpr int EX = 2 * KS - MX;            // and with exponentials
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i) {
+      if (i + AHEAD < 2 * KS) kread(i + AHEAD);
+      nxt.s[i & 1] = mfma32x32x16(kf[i], qf[i >> 1], i < 2 ? zero16 : nxt.s[i & 1]);
+      if (i < MX) {
+#pragma unroll
+        for (int q = 0; q < 4 / MX; ++q) mx = max_piece(mx, cur, i * (4 / MX) + q);
+        if (i == MX - 1) alpha = new_max(mx, m_new);
+      } else {
+        const int j = i - MX;
+#pragma unroll
+        for (int q = 8 * j / EX; q < 8 * (j + 1) / EX; ++q) exp_pair(cur, pk, m_new, rs, q);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    rescale(alpha);
+    pv(cur, pk, m_new, alpha, rs, bv);
+  };
+  auto cold_tile = [&](const Scores& cur, int bv) {   // softmax and P V alone
+    bf16x8 pk[4];
+    float mx = -INFINITY, m_new, rs = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mx = max_piece(mx, cur, q);
+    const float alpha = new_max(mx, m_new);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) exp_pair(cur, pk, m_new, rs, q);
+    rescale(alpha);
+    pv(cur, pk, m_new, alpha, rs, bv);
   };
 
-  int kt = kt0;
-  Tile cur = tile_at(kt);
-  kt = next_kt(kt);
-  {
-    // The first tile's loads are issued unconditionally (a split with no
-    // tile reads row 0 of Q instead, which always exists), so that straight
-    // after them one wait covers exactly the Q fragments.  Without it the
-    // compiler cannot tell at the loop header whether the Q loads are done
-    // and waits for every outstanding load before the first MFMA of each
-    // tile, which also waited for the next tile's prefetch.
-    Tile first = cur;
-    if (!first.nvalid) {
-      first.k = first.v = p.q;
-      first.nvalid = 1;
+  // Tiles are loaded three ahead into four buffers, one barrier per tile:
+  // after tile i's barrier everyone is done with tile i - 1, whose buffer takes
+  // tile i + 3, and tile i + 1 is complete.
+  const int n = t1 - t0;
+  const int np = max(0, min(p.n_pre_tiles - t0, n));   // of them prefix tiles
+  Walk lw = walk_at(t0);
+  int loaded = 0;
+  set_source(lw);
+  const bool loader = tpw == AT_WAVES ? w < 4 : w >= 4;
+  auto load_next = [&]() {
+    if (loader && loaded < n) {
+      load_tile(lw.left, loaded & 3);
+      lw.row += AT_KT;
+      lw.left -= AT_KT;
+      kp += AT_KT * rowbytes;
+      vp += AT_KT * rowbytes;
+      if (lw.left <= 0) {
+        next_run(lw);
+        set_source(lw);
+      }
     }
-    load_tile(first);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * KREG));
+    ++loaded;
+  };
+  auto next_tile = [&](int i) {
+    if (i + 2 < n) wait_loads_and_barrier<2 * PW>();
+    else wait_loads_and_barrier<0>();
+    load_next();
+  };
+  load_next();
+  load_next();
+  load_next();
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // (so the compiler knows that Q is there)
+  wait_loads_and_barrier<0>();
+
+  if (w >= tpw) {   // loads only
+    for (int i = 0; i < n; ++i) next_tile(i);
+    return;
   }
-  while (cur.nvalid) {
-    __syncthreads();  // the previous tile is no longer read
-    if (cur.nvalid == AT_KT)
-      store_tile(AT_KT);
-    else
-      store_tile(cur.nvalid);
-    __syncthreads();
-    // Prefetch the next visible tile while this one is multiplied.
-    const Tile nxt = tile_at(kt);
-    kt = next_kt(kt);
-    if (nxt.nvalid) load_tile(nxt);
-    if (cur.vis) {
-      tile_compute(cur.nvalid);
+  // Prefix tiles, seen by every wavefront (one without a query tile works on
+  // row 0 and stores nothing): the next tile's Q K^T fills the matrix cores
+  // while this tile's softmax runs on the vector unit.
+  {
+    Scores sa, sb;
+    bf16x8 kf[2 * KS];
+    auto hot = [&](Scores& cur, Scores& nxt, int i) {
+      next_tile(i);
+      hot_tile(cur, nxt, (i + 1) & 3, i & 3);
+    };
+    auto last = [&](Scores& cur, int i) {
+      next_tile(i);
+      mask(cur, p.P - (t0 + i) * AT_KT);
+      cold_tile(cur, i & 3);
+    };
+    if (np > 0) {
+      read_k(kf, 0);
+      qk(sa, kf);
+      int i = 0;
+      for (; i + 2 < np; i += 2) {
+        hot(sa, sb, i);
+        hot(sb, sa, i + 1);
+      }
+      if (i + 1 < np) {
+        hot(sa, sb, i);
+        last(sb, i + 1);
+      } else {
+        last(sa, i);
+      }
     }
-    cur = nxt;
+  }
+  // Lane tiles: only those this wavefront's lane sees.
+  if (np < n) {
+    Walk cw = walk_at(t0 + np);
+    for (int i = np; i < n; ++i) {
+      next_tile(i);
+      if (active && (my_vis & cw.m & (0 - cw.m))) {
+        Scores sc;
+        bf16x8 kf[2 * KS];
+        read_k(kf, i & 3);
+        qk(sc, kf);
+        mask(sc, cw.left);
+        cold_tile(sc, i & 3);
+      }
+      cw.left -= AT_KT;
+      if (cw.left <= 0) next_run(cw);
+    }
   }
 
   if (!active || r32 >= nrows) return;
@@ -734,15 +841,9 @@ __global__ __launch_bounds__(256) void prefix_scatter_kernel(const int32_t* idx,
 }
 
 // ------------------------------------------------------------------ host
-static int choose_split(int base_wgs, int total_key_tiles) {
-  // Short grids on the 8-tile kernel leave CUs idle: split the key tiles
-  // until about 256 workgroups exist (one per CU at two wavefronts per
-  // SIMD), keeping at least 3 key tiles per split, since each split adds
-  // partials to merge.  Measured with the merge on 4-wavefront workgroups
-  // (MI355X, best in [1, 16]):
-  // Long 4 splits, 62.8 us (128 us unsplit); Wide 1, 277 us (the LLaDA and
-  // Dream step shapes, 4 and 8 splits here, now take the wavefront-split
-  // kernel).
+// Largest key split of a pass, which sizes its workspace: until about 256
+// workgroups of 8 query tiles exist (one per CU), at least 3 key tiles each.
+static int max_split(int base_wgs, int total_key_tiles) {
   int s = 1;
   while (s < 16 && base_wgs * s < 256 && total_key_tiles >= 3 * (2 * s)) s *= 2;
   return s;
@@ -766,6 +867,32 @@ static PassShape pass_shape(int n_rows, int rows_per_lane, int n_lanes, int g, i
   return s;
 }
 
+// Split and query tiles per workgroup (8, or 4 with the other four wavefronts
+// loading) of a pass on lane_attn_kernel: the cheapest under its times per
+// 64-key tile at D = 128 (MI355X): 1.8 us with 8 query tiles, 1.12 us with 4
+// (D = 64: 1.2 and 0.8), ~5 us per round of one workgroup per CU, and for a
+// split its partials through memory and a merge launch.  4 wins where 8 leave
+// a last round mostly empty or would need a split to fill the chip: window of
+// 2563 rows x 32 heads (352 or 672 workgroups) 153 us against 162 us, 1024
+// rows x 32 heads (128 x 2 splits or 256) 34 us against 40 us.
+static void choose_pass(const PassShape& s, int Hkv, int Hq, int D, int* n_split, int* tpw) {
+  const int most = max_split(s.base_wgs, s.total_key_tiles);
+  double best = 1e30;
+  for (int t = AT_WAVES; t >= 4; t /= 2)
+    for (int ns = 1; ns <= most; ns *= 2) {
+      const long long wgs = (long long)((s.q_tiles_kv + t - 1) / t) * Hkv * ns;
+      const double rounds = (double)((wgs + 255) / 256);
+      const double tile = (t == AT_WAVES ? 1.8 : 1.12) * (D == 64 ? 0.68 : 1.0);
+      double cost = rounds * ((double)((s.total_key_tiles + ns - 1) / ns) * tile + 5.0);
+      if (ns > 1) cost += 4.0 + 4e-6 * ns * s.n_rows * (double)Hq * D / 4.0;
+      if (cost < best) {
+        best = cost;
+        *n_split = ns;
+        *tpw = t;
+      }
+    }
+}
+
 // The wavefront-split kernel when its grid fits the chip in one round (one
 // workgroup per CU: 256 on MI355X) and no wavefront takes more than 8 key
 // units; otherwise the 8-query-tile kernel, whose shared K/V staging wins
@@ -784,25 +911,34 @@ AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh) {
   const int pre_units = (P + 31) / 32;
   const PassShape a = pass_shape(L * B, B, L, g, Hkv, P, B, L);
   pl.wsplit_lane = L > 0 && use_wsplit(a, Hkv, pre_units + L * ((B + 31) / 32));
-  pl.n_split_lane = (L > 0 && !pl.wsplit_lane) ? choose_split(a.base_wgs, a.total_key_tiles) : 1;
-  pl.ws_lane = pl.n_split_lane > 1 ? (size_t)pl.n_split_lane * L * B * Hq * (D * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
+  pl.n_split_lane = pl.n_split_ref = 1;
+  pl.tpw_lane = pl.tpw_ref = AT_WAVES;
+  int most = 1;
+  if (L > 0 && !pl.wsplit_lane) {
+    choose_pass(a, Hkv, Hq, D, &pl.n_split_lane, &pl.tpw_lane);
+    most = max_split(a.base_wgs, a.total_key_tiles);
+  }
+  pl.ws_lane = most > 1 ? (size_t)most * L * B * Hq * (D * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
   pl.wsplit_ref = false;
-  pl.n_split_ref = 1;
   pl.ws_ref = 0;
   if (n_refresh > 0) {
     const int nl = (n_refresh + 31) / 32;
     const PassShape r = pass_shape(n_refresh, 32, nl, g, Hkv, P, 0, 0);
     pl.wsplit_ref = use_wsplit(r, Hkv, pre_units);
-    pl.n_split_ref = pl.wsplit_ref ? 1 : choose_split(r.base_wgs, r.total_key_tiles);
-    pl.ws_ref = pl.n_split_ref > 1 ? (size_t)pl.n_split_ref * n_refresh * Hq * (D * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
+    most = 1;
+    if (!pl.wsplit_ref) {
+      choose_pass(r, Hkv, Hq, D, &pl.n_split_ref, &pl.tpw_ref);
+      most = max_split(r.base_wgs, r.total_key_tiles);
+    }
+    pl.ws_ref = most > 1 ? (size_t)most * n_refresh * Hq * (D * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
   }
   pl.total = pl.ws_lane > pl.ws_ref ? pl.ws_lane : pl.ws_ref;
   return pl;
 }
 
 template <int D>
-static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_split, void* ws,
-                           hipStream_t stream) {
+static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_split, int tpw,
+                           void* ws, hipStream_t stream) {
   AttnParams p = base;
   p.n_rows = s.n_rows;
   p.rows_per_lane = s.rows_per_lane;
@@ -815,7 +951,8 @@ static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_spl
     p.part_o = static_cast<uint16_t*>(ws);
     p.part_ml = reinterpret_cast<float*>(p.part_o + (size_t)n_split * s.n_rows * p.Hq * D);
   }
-  const dim3 grid((s.q_tiles_kv + AT_WAVES - 1) / AT_WAVES, p.Hkv, n_split);
+  p.tpw = tpw;
+  const dim3 grid((s.q_tiles_kv + p.tpw - 1) / p.tpw, p.Hkv, n_split);
   hipLaunchKernelGGL(lane_attn_kernel<D>, grid, dim3(AT_THREADS), 0, stream, p);
   if (n_split > 1) {
     const int nrh = s.n_rows * p.Hq;
@@ -896,8 +1033,8 @@ hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, cons
       e = (D == 64) ? run_pass_wsplit<64, kWsplitWaves>(p, a, stream)
                     : run_pass_wsplit<128, kWsplitWaves>(p, a, stream);
     else
-      e = (D == 64) ? run_pass<64>(p, a, pl.n_split_lane, ws, stream)
-                    : run_pass<128>(p, a, pl.n_split_lane, ws, stream);
+      e = (D == 64) ? run_pass<64>(p, a, pl.n_split_lane, pl.tpw_lane, ws, stream)
+                    : run_pass<128>(p, a, pl.n_split_lane, pl.tpw_lane, ws, stream);
   }
   if (e != hipSuccess || n_refresh <= 0) return e;
 
@@ -917,8 +1054,8 @@ hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, cons
   if (pl.wsplit_ref)
     return (D == 64) ? run_pass_wsplit<64, kWsplitWaves>(r, b, stream)
                      : run_pass_wsplit<128, kWsplitWaves>(r, b, stream);
-  return (D == 64) ? run_pass<64>(r, b, pl.n_split_ref, ws, stream)
-                   : run_pass<128>(r, b, pl.n_split_ref, ws, stream);
+  return (D == 64) ? run_pass<64>(r, b, pl.n_split_ref, pl.tpw_ref, ws, stream)
+                   : run_pass<128>(r, b, pl.n_split_ref, pl.tpw_ref, ws, stream);
 }
 
 }  // namespace al

@@ -10,6 +10,7 @@ namespace al {
 struct AttnPlan {
   bool wsplit_lane, wsplit_ref;  // keys split over the wavefronts of a workgroup
   int n_split_lane, n_split_ref;  // else: key splits over workgroups
+  int tpw_lane, tpw_ref;          // and query tiles per workgroup
   size_t ws_lane, ws_ref, total;
 };
 AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh);

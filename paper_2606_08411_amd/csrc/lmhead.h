@@ -35,19 +35,6 @@ __device__ __forceinline__ void merge_state(float& m, float& s, int& idx, float 
   m = M;
 }
 
-template <int N>
-struct IntTag {
-  static constexpr int value = N;
-};
-
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(IntTag<I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
 struct LmTileParams {
   const uint16_t* hidden;
   const int32_t* row_idx;

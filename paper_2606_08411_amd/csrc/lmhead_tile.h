@@ -39,41 +39,6 @@
 
 namespace al {
 
-// Source of the K elements past d.
-static __device__ __attribute__((aligned(16))) const unsigned char lm_zero_seg[16] = {};
-
-// Direct global->LDS loads of 16 bytes per lane: lane l's bytes land at
-// lds + 16 l.  Inline asm, because the compiler waits for every outstanding
-// load before any LDS read that follows the builtin; the waits are the
-// kernel's own (wait_loads_and_barrier).  No register is written.
-// LDS address lds + LOFF + OFF, global address sbase + voff + OFF.
-template <int LOFF, int OFF, bool NT>
-__device__ __forceinline__ void load_to_lds16(const char* sbase, unsigned voff, unsigned lds) {
-  if (NT)
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4 nt"
-                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc");
-  else
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4"
-                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc");
-}
-// The same with a 64-bit address per lane; LDS address lds + LOFF.
-template <int LOFF>
-__device__ __forceinline__ void load_to_lds16(const char* vaddr, unsigned lds) {
-  asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               ::"s"(lds), "v"(vaddr), "n"(LOFF) : "memory", "scc");
-}
-
-__device__ __forceinline__ const char* uniform_ptr(const char* q) {
-  const unsigned long long v = (unsigned long long)q;
-  return (const char*)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) |
-                       (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v));
-}
-
-template <int N>
-__device__ __forceinline__ void wait_loads_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
 constexpr int tile_stages(int wb, int hb) {
   int s = 2;
   while (s < 6 && (s + 2) * wb + (s + 1) * hb <= 160 * 1024) ++s;
@@ -118,7 +83,7 @@ void lmhead_tile_kernel(LmTileParams p) {
   // (0-3, 12-15, 20-23, 24-27 and so on) then touch every bank once.
   auto swz = [](int r) { return (r & 2) | ((r & 8) >> 1); };
   const unsigned ring0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
-  const char* const zero = reinterpret_cast<const char*>(lm_zero_seg);
+  const char* const zero = reinterpret_cast<const char*>(zero_seg16);
   const char* wp = nullptr;               // W: next stage of its tile (uniform)
   int wk = 0, hk = 0;                     // K stage of the next W / hidden load
   unsigned woff = 0;                      // lane offset in a piece
