@@ -1,4 +1,6 @@
-"""ctypes binding of libasynclane.so (the C ABI in include/asynclane.h).
+"""Binding of libasynclane.so (the C ABI in include/asynclane.h): ctypes, and a
+small CPython module (csrc/fast_call.cpp) that marshals the ordinary case of
+the three calls of a decode step natively (~16 us of Python per call before).
 
 Argument marshalling only: every step of the decode-step hot path runs in the
 library's HIP kernels.  PyTorch supplies device memory and the current HIP
@@ -8,6 +10,8 @@ an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 import threading
 
@@ -16,6 +20,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libasynclane.so")
+FAST_PATH = os.path.join(_HERE, "_fast.so")
 
 AL_OK = 0
 STATUS = {0: "AL_OK", -1: "AL_ERR_NULL", -2: "AL_ERR_SHAPE", -3: "AL_ERR_TREE",
@@ -61,6 +66,7 @@ _SIGNATURES = {
 }
 
 _lib = None
+_fast = None   # the CPython module; its functions return None to decline
 _lock = threading.Lock()
 
 
@@ -69,19 +75,26 @@ class AsyncLaneError(RuntimeError):
 
 
 def library() -> ctypes.CDLL:
-    """Load libasynclane.so (raises when it has not been built)."""
-    global _lib
+    """Load libasynclane.so and _fast.so (raises when they have not been built)."""
+    global _lib, _fast
     with _lock:
         if _lib is None:
-            if not os.path.exists(LIB_PATH):
-                raise AsyncLaneError(
-                    f"{LIB_PATH} is missing: build it with "
-                    "`python -m paper_2606_08411_amd.build` (hipcc, gfx950)")
+            for path in (LIB_PATH, FAST_PATH):
+                if not os.path.exists(path):
+                    raise AsyncLaneError(
+                        f"{path} is missing: build it with "
+                        "`python -m paper_2606_08411_amd.build` (hipcc, gfx950)")
             lib = ctypes.CDLL(LIB_PATH)
             for name, (res, args) in _SIGNATURES.items():
                 fn = getattr(lib, name)
                 fn.restype = res
                 fn.argtypes = args
+            loader = importlib.machinery.ExtensionFileLoader("_fast", FAST_PATH)
+            fast = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fast", loader))
+            loader.exec_module(fast)
+            fast.init({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _SIGNATURES},
+                      _check, _workspace, _raw_stream or _slow_raw_stream)
+            _fast = fast   # before _lib: callers that see _lib use _fast
             _lib = lib
     return _lib
 
@@ -147,6 +160,10 @@ def _call(fn, t, *args):
 # torch's raw-handle accessor costs ~0.1 us against ~3 us for
 # torch.cuda.current_stream(); both name the same stream.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _slow_raw_stream(idx):
+    return torch.cuda.current_stream(idx).cuda_stream
 
 
 def _stream(t=None):
@@ -245,7 +262,11 @@ def lane_attn_forward(q, k_lane, v_lane, k_prefix, v_prefix, parent, B, scale=0.
     A refresh-only call (compact cache refresh) passes q = k_lane = v_lane
     = None and parent = [] with refresh rows.  Returns (o, lse, o_ref,
     lse_ref).  Every tensor's dtype and shape is checked before the call."""
-    lib = library()
+    lib = _lib or library()
+    r = _fast.attn(q, k_lane, v_lane, k_prefix, v_prefix, parent, B, scale, refresh_idx, q_ref,
+                   k_ref, v_ref, o, lse, o_ref, lse_ref, want_lse, workspace)
+    if r is not None:
+        return r
     bf16, f32 = torch.bfloat16, torch.float32
     _tensor(k_prefix, "k_prefix", bf16)
     if k_prefix.dim() != 3:
@@ -374,7 +395,11 @@ def lmhead_confidence(hidden, W, row_idx=None, suppress_eos=None, eos_id=-1,
     int32 device tensor (None = every row).  Output buffers passed in need
     at least N entries (the first N are written).  Returns (conf, argmax,
     lse)."""
-    lib = library()
+    lib = _lib or library()
+    r = _fast.lmhead(hidden, W, None, row_idx, suppress_eos, eos_id, conf, argmax, lse, want_lse,
+                     workspace)
+    if r is not None:
+        return r
     n_rows, d, V, N, conf, argmax, lse = _lmhead_args(hidden, W, row_idx, suppress_eos, conf,
                                                       argmax, lse, want_lse)
     if N == 0:
@@ -423,7 +448,12 @@ def lmhead_confidence_packed(hidden, W_packed, V, row_idx=None, suppress_eos=Non
                              conf=None, argmax=None, lse=None, want_lse=True, workspace=None):
     """lmhead_confidence reading the weight from lmhead_pack_weight's copy
     (V = vocabulary size of the original W; d is hidden's width)."""
-    lib = library()
+    lib = _lib or library()
+    if V is not None:
+        r = _fast.lmhead(hidden, W_packed, V, row_idx, suppress_eos, eos_id, conf, argmax, lse,
+                         want_lse, workspace)
+        if r is not None:
+            return r
     n_rows, d, V, N, conf, argmax, lse = _lmhead_args(hidden, W_packed, row_idx, suppress_eos, conf,
                                                       argmax, lse, want_lse, V=int(V))
     if N == 0:
@@ -471,7 +501,12 @@ def select_unmask(conf, argmax, row_pos, tokens, is_masked, L, B, role, b_len=No
     close_ids; empty = every delimiter counts).  Returns a dict of device
     tensors: unmask_flag, unmasked_pos, still_masked_pos, counts,
     lane_stats, delim_flag."""
-    lib = library()
+    lib = _lib or library()
+    if out is not None and _fast.select(
+            conf, argmax, row_pos, tokens, is_masked, L, B, role, b_len, t_lane, mode, tau,
+            fallback_k, k_lane, delim_ids, eos_id, rho_min, t_min, tau_future, out, digit_ids,
+            open_ids, close_ids):
+        return out
     L, B = int(L), int(B)
     _tensor(row_pos, "row_pos", torch.int32)
     if row_pos.dim() != 1:
