@@ -66,7 +66,13 @@ struct AttnParams {
   float scale_log2;
   int tpw;                 // query tiles (computing wavefronts) per workgroup: 8 or 4
   unsigned long long vis[AT_MAX_LANES];  // bit j: lane block j visible to lane i
+  // Lanes in the order in which the 8-tile kernel deals their query tiles to
+  // workgroups, four to a word.
+  unsigned order[AT_MAX_LANES / 4];
 };
+__device__ __forceinline__ int lane_at(const AttnParams& p, int pos) {
+  return p.n_key_lanes ? (p.order[pos >> 2] >> (8 * (pos & 3))) & 255 : pos;
+}
 
 // Two wavefronts per SIMD (256 registers each), one workgroup per CU.
 //
@@ -88,7 +94,15 @@ struct AttnParams {
 // Per call, same box, graph replay, before -> after: window of 2563 rows x 32
 // heads 195 -> 153 us (D = 64 136 -> 107), 1531 rows x 28 heads on 4 K/V heads
 // 76 -> 50, 1024 rows x 32 heads 42 -> 34, Wide lane + refresh 233 -> 204, Long
-// 43.7 -> 40.
+// 43.7 -> 40.  Then: exponentials pinned between the Q K^T MFMAs, the first V^T
+// fragments read ahead of P V, lane tiles of at most 32 keys computed as
+// halves and lanes dealt depth first: Wide lane + refresh 197.8 -> 192.2 us,
+// Long 36.3 -> 34.4, windows unchanged (their workgroups have one computing
+// wavefront per SIMD).  Counters on the 2563-row window: matrix cores 41% of
+// the cycles, vector unit 35%, no LDS bank conflicts.  Two query tiles per
+// wavefront (half the LDS reads, 512 registers, one wavefront per SIMD) take
+// 57 us at Long and 316 us at Wide: scores pass through accumulation registers
+// and nothing fills a wavefront's waits.
 constexpr int AT_OCC = 2;
 
 template <int D>
@@ -121,8 +135,9 @@ void lane_attn_kernel(AttnParams p) {
   const bool active = w < tpw && qt < p.q_tiles_kv;
   int lane_i = 0, c = 0, hg = 0;
   if (active) {
-    lane_i = qt / per_lane;
-    const int rem = qt - lane_i * per_lane;
+    const int pos = qt / per_lane;
+    const int rem = qt - pos * per_lane;
+    lane_i = lane_at(p, pos);
     c = rem / p.g;
     hg = rem - c * p.g;
   }
@@ -134,7 +149,7 @@ void lane_attn_kernel(AttnParams p) {
   unsigned long long wg_vis = 0ull;
   for (int ww = 0; ww < tpw; ++ww) {
     const int qt2 = blockIdx.x * tpw + ww;
-    if (qt2 < p.q_tiles_kv && p.n_key_lanes) wg_vis |= p.vis[qt2 / per_lane];
+    if (qt2 < p.q_tiles_kv && p.n_key_lanes) wg_vis |= p.vis[lane_at(p, qt2 / per_lane)];
   }
 
   // Q fragments (B operand of S^T = K Q^T), kept in registers.
@@ -244,27 +259,31 @@ void lane_attn_kernel(AttnParams p) {
   struct Scores {
     f32x16 s[2];   // the two 32-key halves
   };
-  auto read_k = [&](bf16x8* kf, int buf) {
+  // (NH = 1: a tile of at most 32 keys, its first half alone.)
+  auto read_k = [&](auto nh_tag, bf16x8* kf, int buf) {
+    constexpr int NH = decltype(nh_tag)::value;
     const char* kt = lds + buf * 2 * TB;
 #pragma unroll
-    for (int i = 0; i < 2 * KS; ++i)
+    for (int i = 0; i < 2 * KS; i += 3 - NH)
       kf[i] = *reinterpret_cast<const bf16x8*>(kt + (ka ^ (32 * (i >> 1))) + (i & 1) * 32 * ROWB);
   };
-  auto qk = [&](Scores& sc, const bf16x8* kf) {
+  auto qk = [&](auto nh_tag, Scores& sc, const bf16x8* kf) {
+    constexpr int NH = decltype(nh_tag)::value;
     const f32x16 zero16 = {};
     // The two accumulation chains interleave, so consecutive MFMAs are independent.
 #pragma unroll
-    for (int i = 0; i < 2 * KS; ++i)
+    for (int i = 0; i < 2 * KS; i += 3 - NH)
       sc.s[i & 1] = mfma32x32x16(kf[i], qf[i >> 1], i < 2 ? zero16 : sc.s[i & 1]);
   };
   auto vfrag = [&](int buf, int ks2, int dt) {
     const uint16_t* a = reinterpret_cast<const uint16_t*>(lds + buf * 2 * TB + TB + (va ^ (64 * dt)) + 16 * ks2 * ROWB);
     return cat_bf16x4(lds_read_tr16(a), lds_read_tr16(a + 8 * D));
   };
-  auto mask = [&](Scores& sc, int nvalid) {
-    if (nvalid < AT_KT) {
+  auto mask = [&](auto nh_tag, Scores& sc, int nvalid) {
+    constexpr int NH = decltype(nh_tag)::value;
+    if (nvalid < 32 * NH) {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NH; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
@@ -313,19 +332,17 @@ void lane_attn_kernel(AttnParams p) {
   // O^T += V^T P^T, one 16-key MFMA step at a time, the second half of P's
   // exponentials between the MFMAs of the first two steps.  The V^T fragment
   // of lane (d, h) is keys 16 ks2 + 4h + {0..3, 8..11} at column d: two
-  // transpose reads of 4 x 16 blocks of the row-major V tile.
-  auto pv = [&](const Scores& sc, bf16x8* pk, float m_new, float alpha, float rs, int buf) {
-    bf16x8 vf[2][DT];
+  // transpose reads of 4 x 16 blocks of the row-major V tile.  vf[0] holds the
+  // first step's fragments.
+  auto pv = [&](auto nh_tag, const Scores& sc, bf16x8* pk, bf16x8 (*vf)[DT], float m_new, float alpha, float rs, int buf) {
+    constexpr int NH = decltype(nh_tag)::value;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[0][dt] = vfrag(buf, 0, dt);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks2 = 0; ks2 < 4; ++ks2) {
+    for (int ks2 = 0; ks2 < 2 * NH; ++ks2) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        if (ks2 < 3) vf[(ks2 + 1) & 1][dt] = vfrag(buf, ks2 + 1, dt);
+        if (ks2 < 2 * NH - 1) vf[(ks2 + 1) & 1][dt] = vfrag(buf, ks2 + 1, dt);
         oacc[dt] = mfma32x32x16(vf[ks2 & 1][dt], pk[ks2], oacc[dt]);
-        if (ks2 < 2) {
+        if (NH == 2 && ks2 < 2) {
 #pragma unroll
           for (int q = 0; q < 4 / DT; ++q) exp_pair(sc, pk, m_new, rs, 8 + ks2 * 4 + dt * (4 / DT) + q);
         }
@@ -337,7 +354,7 @@ void lane_attn_kernel(AttnParams p) {
   // Q K^T of the tile in buffer bq into nxt, with the max and the first half
   // of the exponentials of cur between its MFMAs; then cur's P V.
   auto hot_tile = [&](const Scores& cur, Scores& nxt, int bq, int bv) {
-    bf16x8 kf[2 * KS], pk[4];
+    bf16x8 kf[2 * KS], pk[4], vf[2][DT];
     const f32x16 zero16 = {};
     const char* kt = lds + bq * 2 * TB;
     auto kread = [&](int i) {
@@ -352,6 +369,10 @@ void lane_attn_kernel(AttnParams p) {
 #pragma unroll
     for (int i = 0; i < 2 * KS; ++i) {
       if (i + AHEAD < 2 * KS) kread(i + AHEAD);
+      else if (i + DT >= 2 * KS) {   // the first V^T fragments take the K fragments' registers
+        const int dt = i + DT - 2 * KS;
+        vf[0][dt] = vfrag(bv, 0, dt);
+      }
       nxt.s[i & 1] = mfma32x32x16(kf[i], qf[i >> 1], i < 2 ? zero16 : nxt.s[i & 1]);
       if (i < MX) {
 #pragma unroll
@@ -360,23 +381,33 @@ void lane_attn_kernel(AttnParams p) {
       } else {
         const int j = i - MX;
 #pragma unroll
-        for (int q = 8 * j / EX; q < 8 * (j + 1) / EX; ++q) exp_pair(cur, pk, m_new, rs, q);
+        for (int q = 8 * j / EX; q < 8 * (j + 1) / EX; ++q) {
+          exp_pair(cur, pk, m_new, rs, q);
+          // Left alone, the compiler sinks these past the branch below to their
+          // use in P V, where all 32 exponentials then stand.
+          asm volatile("" ::"v"(__builtin_bit_cast(i32x4, pk[q >> 2])[q & 3]), "v"(rs));
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     rescale(alpha);
-    pv(cur, pk, m_new, alpha, rs, bv);
+    pv(IntTag<2>{}, cur, pk, vf, m_new, alpha, rs, bv);
   };
-  auto cold_tile = [&](const Scores& cur, int bv) {   // softmax and P V alone
+  auto cold_tile = [&](auto nh_tag, const Scores& cur, int bv) {   // softmax and P V alone
+    constexpr int NH = decltype(nh_tag)::value;
     bf16x8 pk[4];
     float mx = -INFINITY, m_new, rs = 0.f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) mx = max_piece(mx, cur, q);
+    for (int q = 0; q < 2 * NH; ++q) mx = max_piece(mx, cur, q);
     const float alpha = new_max(mx, m_new);
 #pragma unroll
     for (int q = 0; q < 8; ++q) exp_pair(cur, pk, m_new, rs, q);
     rescale(alpha);
-    pv(cur, pk, m_new, alpha, rs, bv);
+    bf16x8 vf[2][DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) vf[0][dt] = vfrag(bv, 0, dt);
+    __builtin_amdgcn_sched_barrier(0);
+    pv(nh_tag, cur, pk, vf, m_new, alpha, rs, bv);
   };
 
   // Tiles are loaded three ahead into four buffers, one barrier per tile:
@@ -429,12 +460,12 @@ void lane_attn_kernel(AttnParams p) {
     };
     auto last = [&](Scores& cur, int i) {
       next_tile(i);
-      mask(cur, p.P - (t0 + i) * AT_KT);
-      cold_tile(cur, i & 3);
+      mask(IntTag<2>{}, cur, p.P - (t0 + i) * AT_KT);
+      cold_tile(IntTag<2>{}, cur, i & 3);
     };
     if (np > 0) {
-      read_k(kf, 0);
-      qk(sa, kf);
+      read_k(IntTag<2>{}, kf, 0);
+      qk(IntTag<2>{}, sa, kf);
       int i = 0;
       for (; i + 2 < np; i += 2) {
         hot(sa, sb, i);
@@ -448,18 +479,23 @@ void lane_attn_kernel(AttnParams p) {
       }
     }
   }
-  // Lane tiles: only those this wavefront's lane sees.
+  // Lane tiles: only those this wavefront's lane sees, and of a tile that ends
+  // within its first half (every tile of a block of 32) that half alone.
   if (np < n) {
     Walk cw = walk_at(t0 + np);
     for (int i = np; i < n; ++i) {
       next_tile(i);
       if (active && (my_vis & cw.m & (0 - cw.m))) {
-        Scores sc;
-        bf16x8 kf[2 * KS];
-        read_k(kf, i & 3);
-        qk(sc, kf);
-        mask(sc, cw.left);
-        cold_tile(sc, i & 3);
+        auto lane_tile = [&](auto nh_tag) {
+          Scores sc;
+          bf16x8 kf[2 * KS];
+          read_k(nh_tag, kf, i & 3);
+          qk(nh_tag, sc, kf);
+          mask(nh_tag, sc, cw.left);
+          cold_tile(nh_tag, sc, i & 3);
+        };
+        if (cw.left <= 32) lane_tile(IntTag<1>{});
+        else lane_tile(IntTag<2>{});
       }
       cw.left -= AT_KT;
       if (cw.left <= 0) next_run(cw);
@@ -957,7 +993,7 @@ static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_spl
   if (n_split > 1) {
     const int nrh = s.n_rows * p.Hq;
     const dim3 mgrid((nrh + merge_rows_per_block<D>() - 1) / merge_rows_per_block<D>()), mblock(256);
-    switch (n_split) {  // choose_split returns a power of two <= 16
+    switch (n_split) {  // choose_pass takes a power of two <= 16
       case 2:
         hipLaunchKernelGGL((attn_merge_kernel<D, 2>), mgrid, mblock, 0, stream, p.part_o, p.part_ml, nrh, p.o, p.lse);
         break;
@@ -975,6 +1011,35 @@ static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_spl
     }
   }
   return hipGetLastError();
+}
+
+// Lanes depth first.  A workgroup of the 8-tile kernel loads every lane block
+// that one of its lanes sees, and the fullest workgroup sets the time of a
+// round; neighbours in this order share most of their ancestors.  (32 random
+// lanes of 64 to depth 8, four to a workgroup: at most 11 blocks against 16 in
+// index order; 16 of 32 to depth 6, eight to a workgroup: 12 against 15.)
+// Lane i's parent is the highest of its ancestors (parents come first); any
+// order is correct.
+static void dfs_order(const unsigned long long* vis, int L, unsigned* order) {
+  unsigned long long children[AT_MAX_LANES + 1] = {};   // (the last: roots)
+  for (int i = 0; i < L; ++i) {
+    const unsigned long long anc = vis[i] & ((1ull << i) - 1);
+    children[anc ? 63 - __builtin_clzll(anc) : AT_MAX_LANES] |= 1ull << i;
+  }
+  int stack[AT_MAX_LANES + 1], top = 0, pos = 0;
+  stack[0] = AT_MAX_LANES;
+  while (top >= 0) {
+    unsigned long long& c = children[stack[top]];
+    if (!c) {
+      --top;
+      continue;
+    }
+    const int i = __builtin_ctzll(c);
+    c &= c - 1;
+    order[pos >> 2] |= (unsigned)i << (8 * (pos & 3));
+    ++pos;
+    stack[++top] = i;
+  }
 }
 
 template <int D, int KW>
@@ -1026,6 +1091,7 @@ hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, cons
   p.n_key_lanes = L;
   p.lane_key_tiles = (B + AT_KT - 1) / AT_KT;
   for (int i = 0; i < L; ++i) p.vis[i] = vis[i];
+  if (L > 0 && !pl.wsplit_lane) dfs_order(vis, L, p.order);
   hipError_t e = hipSuccess;
   if (L > 0) {  // L = 0: refresh-only call
     const PassShape a = pass_shape(L * B, B, L, g, Hkv, P, B, L);

@@ -24,6 +24,9 @@ CASES = [  # L, B, P, Hq, Hkv, D, refreshed rows
     (6, 48, 0, 32, 32, 128, 0), (6, 48, 1, 32, 32, 64, 0), (5, 64, 64, 32, 32, 128, 0),
     (5, 80, 130, 28, 4, 128, 13), (9, 32, 200, 32, 32, 128, 20), (9, 96, 320, 16, 16, 64, 0),
     (33, 16, 190, 8, 8, 128, 0), (20, 32, 449, 16, 16, 128, 44), (64, 16, 513, 8, 1, 128, 5),
+    # blocks that end at and past half a key tile, many lanes (dealt depth first)
+    (17, 32, 200, 16, 16, 128, 0), (17, 48, 200, 16, 16, 64, 0), (40, 80, 70, 8, 8, 128, 0),
+    (40, 96, 70, 8, 8, 64, 0),
 ]
 
 
