@@ -620,7 +620,7 @@ def main():
         "lmhead_tflops": round(f_lm / (t_lm * 1e-3) / 1e12, 2),
         "roofline": {
             "kernel": ("lmhead_confidence_packed" if W_packed is not None else "lmhead_confidence")
-                      + " (lmhead_partial_kernel + lmhead_merge_kernel)",
+                      + " (lmhead_tile_kernel + lmhead_merge_kernel)",
             "bound": "hbm",
             "achieved": round(lm_gbs, 1),
             "peak": PEAK_HBM_GBS,
