@@ -169,11 +169,19 @@ void lane_attn_kernel(AttnParams p) {
   float m_run = -INFINITY, l_run = 0.f;
 
   // The workgroup's key tiles: the prefix tiles, then the tiles of the lane
-  // blocks some wavefront sees, in ascending order.  This split takes
-  // [t0, t1) of them.
-  const int n_tiles = p.n_pre_tiles + __popcll(wg_vis) * p.lane_key_tiles;
-  const int t0 = (int)((long long)split * n_tiles / p.n_split);
-  const int t1 = (int)((long long)(split + 1) * n_tiles / p.n_split);
+  // blocks some wavefront sees, in ascending order.  The splits share out all
+  // the call's key tiles, so that which keys a row's partial holds does not
+  // depend on the lanes that share its workgroup; of its share this split takes
+  // the visible ones, [t0, t1) of the workgroup's tiles.
+  auto visible_before = [&](int kt) -> int {
+    if (kt <= p.n_pre_tiles || p.n_key_lanes == 0) return min(kt, p.n_pre_tiles);
+    const int q = kt - p.n_pre_tiles, j = q / p.lane_key_tiles;
+    const unsigned long long below = j < 64 ? wg_vis & ((1ull << j) - 1) : wg_vis;
+    const bool cut = j < 64 && ((wg_vis >> j) & 1);
+    return p.n_pre_tiles + __popcll(below) * p.lane_key_tiles + (cut ? q - j * p.lane_key_tiles : 0);
+  };
+  const int t0 = visible_before((int)((long long)split * p.total_key_tiles / p.n_split));
+  const int t1 = visible_before((int)((long long)(split + 1) * p.total_key_tiles / p.n_split));
   // They come in runs of consecutive rows: the prefix, then each block.  A
   // walk holds what is left of its run, so that the next tile costs a few
   // scalar operations; the rest is done once per run.

@@ -61,3 +61,22 @@ def test_key_tile_edges(case):
     if n_ref:
         assert np.abs(out["o_ref"] - ref["o_ref"]).max() < TOL_O
         assert np.abs(out["lse_ref"] - ref["lse_ref"]).max() < TOL_LSE
+
+
+def test_rounding_does_not_depend_on_the_other_lanes():
+    """With key splits, which keys a partial holds is a matter of the call's sizes: the result of a
+    lane that only sees itself has the same bits whatever the other lanes of its workgroup see."""
+    import paper_2606_08411_amd as al
+    import torch
+    from gpu_util import dev_bf16
+    L, B = 20, 32
+    step = synth.make_step("tiny", 5, with_weight=False, D=128, B=B, L=L, tree="linear", Hq=16,
+                           Hkv=16, P=449, V=64, d=64)
+    a = [dev_bf16(x) for x in (step.q, step.k_lane, step.v_lane, step.k_pre, step.v_pre)]
+    got = []
+    for parent in ([-1] * L, list(range(-1, L - 2)) + [-1]):   # alone / a chain, the last lane alone
+        o, lse, _, _ = al.lane_attn_forward(*a, parent, B)
+        got.append((o[-B:].clone(), lse[-B:].clone()))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])
