@@ -59,6 +59,15 @@ size_t lane_attn_workspace_size(int L, int B, int P, int Hq, int Hkv, int D, int
   return al::attn_plan(L, B, P, Hq, Hkv, D, n_refresh).total;
 }
 
+int al::al_internal_attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh, int32_t* out) {
+  if (!attn_shape_ok(L, B, P, Hq, Hkv, D, n_refresh)) return AL_ERR_SHAPE;
+  const al::AttnPlan p = al::attn_plan(L, B, P, Hq, Hkv, D, n_refresh);
+  const int32_t v[8] = {p.wsplit_lane, p.lane.n_split, p.lane.tpw, p.lane.f32,
+                        p.wsplit_ref,  p.ref.n_split,  p.ref.tpw,  p.ref.f32};
+  for (int i = 0; i < 8; ++i) out[i] = v[i];
+  return AL_OK;
+}
+
 int lane_attn_forward(const al_bf16* q, const al_bf16* k_lane, const al_bf16* v_lane,
                       al_bf16* k_prefix, al_bf16* v_prefix, const int32_t* parent, int L, int B,
                       int P, int Hq, int Hkv, int D, float scale, const int32_t* refresh_idx,

@@ -30,7 +30,8 @@
 // combines.  The partial outputs are kept in bf16 (the softmax statistics
 // in fp32): one rounding of a value that the output rounds to bf16 again,
 // for half the partial traffic (Long shape, 4 splits: 49-51 -> 46.4 us per
-// call, MI355X; outputs move by at most one bf16 step).
+// call, MI355X; outputs move by at most one bf16 step).  Fewer splits than the
+// workspace is sized for keep them in fp32, which its bytes hold.
 #include <math.h>
 
 #include "common.h"
@@ -58,8 +59,9 @@ struct AttnParams {
   const uint16_t* v_pre;
   uint16_t* o;             // [n_rows][Hq][D]
   float* lse;              // [n_rows][Hq] or null
-  uint16_t* part_o;        // [n_split][n_rows][Hq][D] bf16, unnormalised, when n_split > 1
+  void* part_o;            // [n_split][n_rows][Hq][D] bf16 or fp32, unnormalised, when n_split > 1
   float* part_ml;          // [n_split][n_rows][Hq][2]
+  bool part_f32;
   int n_rows, rows_per_lane, tiles_per_lane, q_tiles_kv;
   int P, Hq, Hkv, g;
   int B_keys, n_key_lanes, lane_key_tiles, n_pre_tiles, total_key_tiles, n_split;
@@ -526,15 +528,23 @@ void lane_attn_kernel(AttnParams p) {
       }
     if (p.lse && hh == 0) p.lse[orow] = (m_run + log2f(l_run)) * AT_LN2;
   } else {
-    uint16_t* po = p.part_o + ((size_t)split * p.n_rows * p.Hq + orow) * D;
+    const size_t prow = ((size_t)split * p.n_rows * p.Hq + orow) * D;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg) {
-        bf16x4 v4;
+        const size_t at = prow + dt * 32 + 8 * rg + 4 * hh;
+        if (p.part_f32) {
+          f32x4 v4;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v4[e] = (__bf16)oacc[dt][rg * 4 + e];
-        *reinterpret_cast<bf16x4*>(po + dt * 32 + 8 * rg + 4 * hh) = v4;
+          for (int e = 0; e < 4; ++e) v4[e] = oacc[dt][rg * 4 + e];
+          *reinterpret_cast<f32x4*>(static_cast<float*>(p.part_o) + at) = v4;
+        } else {
+          bf16x4 v4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v4[e] = (__bf16)oacc[dt][rg * 4 + e];
+          *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(p.part_o) + at) = v4;
+        }
       }
     if (hh == 0) {
       float* pm = p.part_ml + ((size_t)split * p.n_rows * p.Hq + orow) * 2;
@@ -829,8 +839,8 @@ void lane_attn_wsplit_kernel(AttnParams p) {
 // trip); the splits are summed in ascending order.
 template <int D>
 constexpr int merge_rows_per_block() { return 256 / (D / 8); }
-template <int D, int NS>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t* part_o, const float* part_ml,
+template <int D, int NS, class T>   // T: uint16_t (bf16) or float partials
+__global__ __launch_bounds__(256) void attn_merge_kernel(const T* part_o, const float* part_ml,
                                                          int n_rowheads, uint16_t* o, float* lse) {
   constexpr int LPR = D / 8;  // lanes per (row, head)
   const int rh = blockIdx.x * merge_rows_per_block<D>() + threadIdx.x / LPR;
@@ -842,9 +852,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t* part_o,
     const float2 ml = *reinterpret_cast<const float2*>(part_ml + ((size_t)s * n_rowheads + rh) * 2);
     m[s] = ml.x;
     l[s] = ml.y;
-    const bf16x8 v = load_bf16x8(part_o + ((size_t)s * n_rowheads + rh) * D + sl * 8);
+    const T* src = part_o + ((size_t)s * n_rowheads + rh) * D + sl * 8;
+    if constexpr (sizeof(T) == 4) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(src), b = *reinterpret_cast<const f32x4*>(src + 4);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) po[s][e] = (float)v[e];
+      for (int e = 0; e < 8; ++e) po[s][e] = e < 4 ? a[e] : b[e - 4];
+    } else {
+      const bf16x8 v = load_bf16x8(src);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) po[s][e] = (float)v[e];
+    }
   }
   float M = -INFINITY;
 #pragma unroll
@@ -919,7 +936,11 @@ static PassShape pass_shape(int n_rows, int rows_per_lane, int n_lanes, int g, i
 // a last round mostly empty or would need a split to fill the chip: window of
 // 2563 rows x 32 heads (352 or 672 workgroups) 153 us against 162 us, 1024
 // rows x 32 heads (128 x 2 splits or 256) 34 us against 40 us.
-static void choose_pass(const PassShape& s, int Hkv, int Hq, int D, int* n_split, int* tpw) {
+//
+// Fewer splits than max_split hold other keys per partial; in bf16 that moves the
+// output 0.4 to 1.4% further from the 64-bit one (relative error 2.84e-3 -> 2.86e-3
+// over 3333 keys), so those partials are fp32 (2.33e-3).
+static void choose_pass(const PassShape& s, int Hkv, int Hq, int D, AttnPass* pass) {
   const int most = max_split(s.base_wgs, s.total_key_tiles);
   double best = 1e30;
   for (int t = AT_WAVES; t >= 4; t /= 2)
@@ -928,11 +949,10 @@ static void choose_pass(const PassShape& s, int Hkv, int Hq, int D, int* n_split
       const double rounds = (double)((wgs + 255) / 256);
       const double tile = (t == AT_WAVES ? 1.8 : 1.12) * (D == 64 ? 0.68 : 1.0);
       double cost = rounds * ((double)((s.total_key_tiles + ns - 1) / ns) * tile + 5.0);
-      if (ns > 1) cost += 4.0 + 4e-6 * ns * s.n_rows * (double)Hq * D / 4.0;
+      if (ns > 1) cost += 4.0 + 1e-6 * ns * s.n_rows * (double)Hq * D;
       if (cost < best) {
         best = cost;
-        *n_split = ns;
-        *tpw = t;
+        *pass = AttnPass{ns, t, ns > 1 && ns < most};
       }
     }
 }
@@ -955,11 +975,10 @@ AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh) {
   const int pre_units = (P + 31) / 32;
   const PassShape a = pass_shape(L * B, B, L, g, Hkv, P, B, L);
   pl.wsplit_lane = L > 0 && use_wsplit(a, Hkv, pre_units + L * ((B + 31) / 32));
-  pl.n_split_lane = pl.n_split_ref = 1;
-  pl.tpw_lane = pl.tpw_ref = AT_WAVES;
+  pl.lane = pl.ref = AttnPass{1, AT_WAVES, false};
   int most = 1;
   if (L > 0 && !pl.wsplit_lane) {
-    choose_pass(a, Hkv, Hq, D, &pl.n_split_lane, &pl.tpw_lane);
+    choose_pass(a, Hkv, Hq, D, &pl.lane);
     most = max_split(a.base_wgs, a.total_key_tiles);
   }
   pl.ws_lane = most > 1 ? (size_t)most * L * B * Hq * (D * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
@@ -971,7 +990,7 @@ AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh) {
     pl.wsplit_ref = use_wsplit(r, Hkv, pre_units);
     most = 1;
     if (!pl.wsplit_ref) {
-      choose_pass(r, Hkv, Hq, D, &pl.n_split_ref, &pl.tpw_ref);
+      choose_pass(r, Hkv, Hq, D, &pl.ref);
       most = max_split(r.base_wgs, r.total_key_tiles);
     }
     pl.ws_ref = most > 1 ? (size_t)most * n_refresh * Hq * (D * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
@@ -981,8 +1000,9 @@ AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh) {
 }
 
 template <int D>
-static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_split, int tpw,
+static hipError_t run_pass(const AttnParams& base, const PassShape& s, const AttnPass& pass,
                            void* ws, hipStream_t stream) {
+  const int n_split = pass.n_split;
   AttnParams p = base;
   p.n_rows = s.n_rows;
   p.rows_per_lane = s.rows_per_lane;
@@ -992,31 +1012,37 @@ static hipError_t run_pass(const AttnParams& base, const PassShape& s, int n_spl
   p.total_key_tiles = s.total_key_tiles;
   p.n_split = n_split;
   if (n_split > 1) {
-    p.part_o = static_cast<uint16_t*>(ws);
-    p.part_ml = reinterpret_cast<float*>(p.part_o + (size_t)n_split * s.n_rows * p.Hq * D);
+    const size_t n = (size_t)n_split * s.n_rows * p.Hq * D;
+    p.part_o = ws;
+    p.part_f32 = pass.f32;
+    p.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + n * (pass.f32 ? 4 : 2));
   }
-  p.tpw = tpw;
+  p.tpw = pass.tpw;
   const dim3 grid((s.q_tiles_kv + p.tpw - 1) / p.tpw, p.Hkv, n_split);
   hipLaunchKernelGGL(lane_attn_kernel<D>, grid, dim3(AT_THREADS), 0, stream, p);
   if (n_split > 1) {
     const int nrh = s.n_rows * p.Hq;
     const dim3 mgrid((nrh + merge_rows_per_block<D>() - 1) / merge_rows_per_block<D>()), mblock(256);
-    switch (n_split) {  // choose_pass takes a power of two <= 16
+#define AL_MERGE(NS, T) \
+  hipLaunchKernelGGL((attn_merge_kernel<D, NS, T>), mgrid, mblock, 0, stream, \
+                     static_cast<const T*>(p.part_o), p.part_ml, nrh, p.o, p.lse)
+    switch (n_split) {  // choose_pass takes a power of two <= 16, in fp32 <= 8
       case 2:
-        hipLaunchKernelGGL((attn_merge_kernel<D, 2>), mgrid, mblock, 0, stream, p.part_o, p.part_ml, nrh, p.o, p.lse);
+        if (pass.f32) AL_MERGE(2, float); else AL_MERGE(2, uint16_t);
         break;
       case 4:
-        hipLaunchKernelGGL((attn_merge_kernel<D, 4>), mgrid, mblock, 0, stream, p.part_o, p.part_ml, nrh, p.o, p.lse);
+        if (pass.f32) AL_MERGE(4, float); else AL_MERGE(4, uint16_t);
         break;
       case 8:
-        hipLaunchKernelGGL((attn_merge_kernel<D, 8>), mgrid, mblock, 0, stream, p.part_o, p.part_ml, nrh, p.o, p.lse);
+        if (pass.f32) AL_MERGE(8, float); else AL_MERGE(8, uint16_t);
         break;
       case 16:
-        hipLaunchKernelGGL((attn_merge_kernel<D, 16>), mgrid, mblock, 0, stream, p.part_o, p.part_ml, nrh, p.o, p.lse);
+        AL_MERGE(16, uint16_t);
         break;
       default:
         return hipErrorInvalidValue;
     }
+#undef AL_MERGE
   }
   return hipGetLastError();
 }
@@ -1107,8 +1133,8 @@ hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, cons
       e = (D == 64) ? run_pass_wsplit<64, kWsplitWaves>(p, a, stream)
                     : run_pass_wsplit<128, kWsplitWaves>(p, a, stream);
     else
-      e = (D == 64) ? run_pass<64>(p, a, pl.n_split_lane, pl.tpw_lane, ws, stream)
-                    : run_pass<128>(p, a, pl.n_split_lane, pl.tpw_lane, ws, stream);
+      e = (D == 64) ? run_pass<64>(p, a, pl.lane, ws, stream)
+                    : run_pass<128>(p, a, pl.lane, ws, stream);
   }
   if (e != hipSuccess || n_refresh <= 0) return e;
 
@@ -1128,8 +1154,8 @@ hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, cons
   if (pl.wsplit_ref)
     return (D == 64) ? run_pass_wsplit<64, kWsplitWaves>(r, b, stream)
                      : run_pass_wsplit<128, kWsplitWaves>(r, b, stream);
-  return (D == 64) ? run_pass<64>(r, b, pl.n_split_ref, pl.tpw_ref, ws, stream)
-                   : run_pass<128>(r, b, pl.n_split_ref, pl.tpw_ref, ws, stream);
+  return (D == 64) ? run_pass<64>(r, b, pl.ref, ws, stream)
+                   : run_pass<128>(r, b, pl.ref, ws, stream);
 }
 
 }  // namespace al

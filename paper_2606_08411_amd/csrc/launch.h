@@ -7,13 +7,20 @@
 namespace al {
 
 // ---- lane attention
+struct AttnPass {
+  int n_split;   // key splits over workgroups
+  int tpw;       // query tiles per workgroup
+  bool f32;      // partial outputs of the splits in fp32 (else bf16)
+};
 struct AttnPlan {
   bool wsplit_lane, wsplit_ref;  // keys split over the wavefronts of a workgroup
-  int n_split_lane, n_split_ref;  // else: key splits over workgroups
-  int tpw_lane, tpw_ref;          // and query tiles per workgroup
+  AttnPass lane, ref;            // else
   size_t ws_lane, ws_ref, total;
 };
 AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh);
+// For tests: {wavefront split, key splits, query tiles per workgroup, fp32
+// partials} of the lane pass, then of the refresh pass.
+extern "C" int al_internal_attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh, int32_t* out);
 
 hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, const uint16_t* v_lane,
                                  uint16_t* k_pre, uint16_t* v_pre, const unsigned long long* vis,

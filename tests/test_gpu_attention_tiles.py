@@ -1,10 +1,12 @@
-"""The 8-tile attention kernel at the edges of its key-tile ring: 0 to 9 prefix
+"""The 8-tile attention kernel at the edges of its key-tile ring: 0 to 24 prefix
 tiles of 64 keys (odd and even, full and ragged), lane blocks of 1 and 2 tiles,
-workgroups of 8 and of 4 query tiles, with and without key splits.
+and every number of key splits and of query tiles per workgroup that the plan
+chooses, for lanes and for refreshed rows (test_plans_host.py checks that).
 
 Against the fp64 oracle; outputs are bf16 (half a step of the largest values
 met, below 4, is 2^-8) and P is rounded to bf16 (relative 2^-9 of a convex
-combination of values below 5): within 2e-2.  LSE within 2e-3.
+combination of values below 5): within 2e-2.  LSE within 2e-3: a rounded P moves it
+by at most 2^-8 of that key's share, and the smallest case has 40 keys.
 """
 import numpy as np
 import pytest
@@ -27,6 +29,14 @@ CASES = [  # L, B, P, Hq, Hkv, D, refreshed rows
     # blocks that end at and past half a key tile, many lanes (dealt depth first)
     (17, 32, 200, 16, 16, 128, 0), (17, 48, 200, 16, 16, 64, 0), (40, 80, 70, 8, 8, 128, 0),
     (40, 96, 70, 8, 8, 64, 0),
+    # 8 query tiles unsplit; 2 to 16 splits of lanes, some starting inside the lane
+    # tiles; refreshed rows with 8 query tiles, with 2 and with 4 splits
+    (5, 16, 65, 224, 32, 64, 0), (16, 16, 65, 28, 4, 64, 0), (33, 16, 130, 16, 16, 64, 0),
+    (64, 16, 65, 16, 16, 64, 0), (17, 16, 65, 16, 16, 64, 0), (33, 48, 65, 2, 2, 64, 0),
+    (8, 80, 1300, 1, 1, 128, 0), (33, 16, 1300, 2, 2, 64, 0), (64, 16, 65, 4, 4, 64, 0),
+    (33, 16, 1300, 4, 2, 128, 0), (33, 16, 1300, 1, 1, 64, 0), (40, 16, 1300, 2, 2, 64, 0),
+    (9, 16, 65, 32, 16, 128, 0), (0, 16, 200, 224, 32, 64, 129), (0, 16, 1000, 14, 2, 64, 669),
+    (0, 16, 1000, 56, 8, 64, 129), (0, 16, 1500, 112, 16, 128, 65),
 ]
 
 
@@ -80,3 +90,28 @@ def test_rounding_does_not_depend_on_the_other_lanes():
     torch.cuda.synchronize()
     assert torch.equal(got[0][0], got[1][0])
     assert torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("case", [(9, 32, 3333, 32, 8, 128), (12, 64, 1500, 8, 2, 128)], ids=str)
+def test_fewer_splits_keep_fp32_partials(case):
+    """Rounding P (bf16) and the output (bf16) each give a relative error of about 2^-9 / sqrt(1.4) =
+    1.65e-3, 2.33e-3 together (2-norms); bf16 partials would add a third, 2.85e-3 in all."""
+    import paper_2606_08411_amd as al
+    import torch
+    L, B, P, Hq, Hkv, D = case
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    mk = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    q, kl, vl, kp, vp = mk(L * B, Hq, D), mk(L * B, Hkv, D), mk(L * B, Hkv, D), mk(P, Hkv, D), mk(P, Hkv, D)
+    o, _, _, _ = al.lane_attn_forward(q, kl, vl, kp, vp, list(range(-1, L - 1)), B)   # a chain
+    see = torch.ones((L, L), device="cuda").tril().bool().repeat_interleave(B, 0).repeat_interleave(B, 1)
+    see = torch.cat([torch.ones((L * B, P), dtype=torch.bool, device="cuda"), see], 1)
+    num = den = 0.0
+    for h in range(Hq):
+        k = torch.cat([kp[:, h // (Hq // Hkv)], kl[:, h // (Hq // Hkv)]]).double()
+        v = torch.cat([vp[:, h // (Hq // Hkv)], vl[:, h // (Hq // Hkv)]]).double()
+        z = torch.mm(q[:, h].double(), k.t().contiguous()) / D ** 0.5
+        ref = torch.mm(torch.softmax(z.masked_fill(~see, -float("inf")), 1), v)
+        num += float((o[:, h].double() - ref).pow(2).sum())
+        den += float(ref.pow(2).sum())
+    assert (num / den) ** 0.5 < 2.6e-3

@@ -1,0 +1,65 @@
+"""The plans behind the calls, on the host: which kernels and layouts the sizes choose, that the
+GPU tests' cases reach all of them, and that a plan's workspace holds what it writes."""
+import ctypes
+import random
+
+import pytest
+
+import test_gpu_attention_tiles
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2606_08411_amd import _lib
+    return _lib.library()
+
+
+def attn_plan(lib, L, B, P, Hq, Hkv, D, n_ref):
+    """[lane pass, refresh pass], each (wavefront split, key splits, query tiles, fp32 partials)."""
+    out = (ctypes.c_int32 * 8)()
+    assert lib.al_internal_attn_plan(L, B, P, Hq, Hkv, D, n_ref, out) == 0
+    return tuple(out[:4]), tuple(out[4:])
+
+
+def _attn_sizes(n, seed):
+    r = random.Random(seed)
+    for _ in range(n):
+        Hkv, g = r.choice([1, 2, 4, 8, 16, 32]), r.choice([1, 1, 2, 4, 7])
+        P, D = r.choice([0, 1, 65, 130, 200, 449, 700, 1300, 3000]), r.choice([64, 128])
+        L = r.choice([0, 1, 2, 3, 5, 8, 9, 16, 17, 20, 33, 40, 64])
+        n_ref = r.randint(0 if L else 1, P) if P else 0
+        if L or n_ref:
+            yield L, r.choice([16, 32, 48, 80]), P, Hkv * g, Hkv, D, n_ref
+
+
+def test_attention_cases_reach_every_plan(lib):
+    """(pass, key splits, query tiles, fp32 partials) of the 8-tile kernel."""
+    def kinds(case):
+        lane, ref = attn_plan(lib, *case)
+        if case[0] and not lane[0]:
+            yield ("lane",) + lane[1:]
+        if case[6] and not ref[0]:
+            yield ("refresh",) + ref[1:]
+    met = {k for c in _attn_sizes(40000, 1) for k in kinds(c)}
+    tested = {k for c in test_gpu_attention_tiles.CASES for k in kinds(c)}
+    # refreshed rows split otherwise than below take thousands of keys times heads: they run the
+    # instances that the lanes' cases run, the workgroup does not know which pass it is in
+    met = {k for k in met if k[0] == "lane" or ("lane",) + k[1:] not in tested}
+    assert met <= tested, sorted(met - tested)
+
+
+def test_attention_workspace_holds_the_partials(lib):
+    """Splits write [n_split][rows][Hq] x (D bf16 or fp32 + 2 fp32); fp32 only with fewer splits than
+    the workspace is sized for."""
+    n = 0
+    for c in _attn_sizes(40000, 2):
+        L, B, P, Hq, Hkv, D, n_ref = c
+        ws = lib.lane_attn_workspace_size(*c)
+        for (wsplit, ns, tpw, f32), rows in zip(attn_plan(lib, *c), (L * B, n_ref)):
+            if rows and ns > 1:
+                assert not wsplit
+                assert ns * rows * Hq * ((4 if f32 else 2) * D + 8) <= ws, c
+                n += f32
+            else:
+                assert not f32
+    assert n > 100
