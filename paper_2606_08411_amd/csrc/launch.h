@@ -42,6 +42,11 @@ hipError_t launch_lmhead(const uint16_t* hidden, const int32_t* row_idx, int N, 
                          int32_t* argmax, float* lse, void* ws, hipStream_t stream,
                          bool packed = false);
 size_t lmhead_packed_bytes(int d, int V);
+// For tests: {64-row units and 16-column units of a tile, vocabulary tiles,
+// column tiles, ragged, non-temporal, two barriers per stage, partials fit the
+// workspace} of a call; the (RA, CBT) built, at most `most` pairs.
+extern "C" int al_internal_lmhead_plan(int N, int d, int V, int packed, int32_t* out);
+extern "C" int al_internal_lmhead_instances(int32_t* out, int most);
 hipError_t launch_lmhead_pack(const uint16_t* W, int d, int V, uint16_t* Wp, hipStream_t stream);
 
 // ---- selection

@@ -57,8 +57,13 @@ struct LmTileParams {
   X(5, 4) X(5, 6) X(5, 8) X(5, 9) X(5, 10) X(5, 11) X(5, 12) X(5, 13)                       \
   X(8, 2) X(8, 4) X(8, 6)
 
-// Launch one instance (nt: W loaded non-temporally).
+// Which variant of an instance a call takes.
+struct LmVariant {
+  bool packed;
+  bool ragged;   // loads with per-lane addresses: K past d, W rows past V in an 8-row piece
+  bool nt;       // W loaded non-temporally
+};
 template <int RA, int CBT>
-void launch_lmhead_tile(const LmTileParams& p, bool packed, bool nt, dim3 grid, hipStream_t stream);
+void launch_lmhead_tile(const LmTileParams& p, LmVariant v, dim3 grid, hipStream_t stream);
 
 }  // namespace al

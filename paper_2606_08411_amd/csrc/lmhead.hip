@@ -91,7 +91,7 @@ static int lm_cu_count() {
 // One layout: tiles of 64 ra vocabulary rows x 16 cbt columns.
 struct LmLayout {
   int ra, cbt, n_vt, n_nt;
-  bool nt;   // W loaded non-temporally
+  LmVariant var;
   size_t bytes() const { return sizeof(LmPartial) * (size_t)n_nt * n_vt * 16 * cbt; }
 };
 
@@ -149,7 +149,7 @@ size_t lmhead_workspace_bytes(int N, int d, int V) {
 // workgroups (V = 152064: RA = 5 at 128 columns 178 us, RA = 4 202; V =
 // 126464: RA = 4 170, RA = 5 192), and small vocabularies the smallest tiles
 // (V = 16384, N = 32: RA = 1 28 us, 2 36, 4 50).
-static LmLayout lm_layout(int N, int d, int V) {
+static LmLayout lm_layout(int N, int d, int V, bool packed) {
   const int cus = lm_cu_count();
   const int units = (V + 31) / 32, frags = (N + 15) / 16;
   const double stages = (d + 63) / 64;
@@ -158,7 +158,7 @@ static LmLayout lm_layout(int N, int d, int V) {
   LmLayout best{};
   double best_t = 1e30;
   for (const auto& in : kLmInstances) {
-    const LmLayout c{in.ra, in.cbt, (units + 2 * in.ra - 1) / (2 * in.ra), (frags + in.cbt - 1) / in.cbt, false};
+    const LmLayout c{in.ra, in.cbt, (units + 2 * in.ra - 1) / (2 * in.ra), (frags + in.cbt - 1) / in.cbt, {}};
     if (c.bytes() > limit) continue;
     const long long tiles = (long long)c.n_vt * c.n_nt;
     const double rounds = (double)((tiles + cus - 1) / cus);
@@ -173,12 +173,33 @@ static LmLayout lm_layout(int N, int d, int V) {
       best = c;
     }
   }
+  best.var.packed = packed;
+  best.var.ragged = d % 64 != 0 || (!packed && V % 8 != 0);
   // Non-temporal loads where every element of W is read once and W exceeds
   // the 256 MB memory-side cache anyway (packed weight only: pieces of 1 KB.
   // V = 65536: 92 us against 122 us for W as given; below, caching wins: V =
-  // 16384 34 us non-temporal, 29 us cached).
-  best.nt = best.n_nt == 1 && w_bytes > 384.0e6;
+  // 16384 34 us non-temporal, 29 us cached; ragged K too: V = 126464, d = 4072,
+  // N = 96 191 us cached, 156 us non-temporal).
+  best.var.nt = packed && best.n_nt == 1 && w_bytes > 384.0e6;
   return best;
+}
+
+int al_internal_lmhead_plan(int N, int d, int V, int packed, int32_t* out) {
+  const LmLayout L = lm_layout(N, d, V, packed != 0);
+  const int32_t v[8] = {L.ra, L.cbt, L.n_vt, L.n_nt, L.var.ragged, L.var.nt, 0,
+                        L.ra != 0 && L.bytes() <= lmhead_workspace_bytes(N, d, V)};
+  std::copy(v, v + 8, out);
+  return 0;
+}
+
+int al_internal_lmhead_instances(int32_t* out, int most) {
+  int n = 0;
+  for (const auto& in : kLmInstances)
+    if (n < most) {
+      out[2 * n] = in.ra;
+      out[2 * n++ + 1] = in.cbt;
+    }
+  return n;
 }
 
 // Partials of lmhead_confidence_noalloc.  In host code `scratch` names a
@@ -247,7 +268,7 @@ hipError_t launch_lmhead(const uint16_t* hidden, const int32_t* row_idx, int N,
                          float* conf, int32_t* argmax, float* lse, void* ws,
                          hipStream_t stream, bool packed) {
   if (N <= 0) return hipSuccess;
-  const LmLayout L = lm_layout(N, d, V);
+  const LmLayout L = lm_layout(N, d, V, packed);
   LmTileParams p{};
   p.hidden = hidden;
   p.row_idx = row_idx;
@@ -266,10 +287,9 @@ hipError_t launch_lmhead(const uint16_t* hidden, const int32_t* row_idx, int N,
   // At most one workgroup per CU, dealt to the 8 XCDs in contiguous runs of
   // tiles (the column tiles of a vocabulary tile share that XCD's L2).
   const dim3 grid(8 * std::min(p.tiles_per_xcd, std::max(1, lm_cu_count() / 8)));
-  const bool nt = packed && L.nt;
   switch (L.ra * 32 + L.cbt) {
 #define AL_LM_X(RA, CBT) \
-  case RA * 32 + CBT: launch_lmhead_tile<RA, CBT>(p, packed, nt, grid, stream); break;
+  case RA * 32 + CBT: launch_lmhead_tile<RA, CBT>(p, L.var, grid, stream); break;
     AL_LM_INSTANCES(AL_LM_X)
 #undef AL_LM_X
     default: return hipErrorInvalidValue;

@@ -361,25 +361,22 @@ void lmhead_tile_kernel(LmTileParams p) {
 }
 // ------------------------------------------------------------------ host
 template <int RA, int CBT>
-void launch_lmhead_tile(const LmTileParams& p, bool packed, bool nt, dim3 grid, hipStream_t stream) {
-  const dim3 block(512);
-  // K past d (d % 64 != 0) and, on W as given, rows past V inside an 8-row
-  // piece need per-lane addresses.
-  const bool ragged = p.d % 64 != 0 || (!packed && p.V % 8 != 0);
+void launch_lmhead_tile(const LmTileParams& p, LmVariant v, dim3 grid, hipStream_t stream) {
 #define AL_LM_TILE(RG, PK, NTL) \
-  hipLaunchKernelGGL((lmhead_tile_kernel<RA, CBT, RG, PK, NTL>), grid, block, 0, stream, p)
-  if (packed) {
-    if (ragged) AL_LM_TILE(true, true, false);
-    else if (nt) AL_LM_TILE(false, true, true);
-    else AL_LM_TILE(false, true, false);
-  } else {
-    if (ragged) AL_LM_TILE(true, false, false);
+  hipLaunchKernelGGL((lmhead_tile_kernel<RA, CBT, RG, PK, NTL>), grid, dim3(512), 0, stream, p)
+  if (!v.packed) {
+    if (v.ragged) AL_LM_TILE(true, false, false);
     else AL_LM_TILE(false, false, false);
+  } else if (v.nt) {
+    if (v.ragged) AL_LM_TILE(true, true, true);
+    else AL_LM_TILE(false, true, true);
+  } else {
+    if (v.ragged) AL_LM_TILE(true, true, false);
+    else AL_LM_TILE(false, true, false);
   }
 #undef AL_LM_TILE
 }
-
 #define AL_LM_INSTANCE(RA, CBT) \
-  template void launch_lmhead_tile<RA, CBT>(const LmTileParams&, bool, bool, dim3, hipStream_t);
+  template void launch_lmhead_tile<RA, CBT>(const LmTileParams&, LmVariant, dim3, hipStream_t);
 
 }  // namespace al

@@ -1,6 +1,7 @@
 """The plans behind the calls, on the host: which kernels and layouts the sizes choose, that the
 GPU tests' cases reach all of them, and that a plan's workspace holds what it writes."""
 import ctypes
+import math
 import random
 
 import pytest
@@ -63,3 +64,37 @@ def test_attention_workspace_holds_the_partials(lib):
             else:
                 assert not f32
     assert n > 100
+
+
+def lmhead_plan(lib, N, d, V, packed):
+    """(RA, CBT, vocabulary tiles, column tiles, ragged, non-temporal, two barriers per stage, fits)."""
+    out = (ctypes.c_int32 * 8)()
+    assert lib.al_internal_lmhead_plan(N, d, V, int(packed), out) == 0
+    return tuple(out)
+
+
+def _log_int(r, lo, hi):
+    return int(round(math.exp(r.uniform(math.log(lo), math.log(hi)))))
+
+
+def test_lmhead_every_size_has_a_layout(lib):
+    """Some instance's partials always fit the workspace that the size query names, also where the
+    no-alloc twin's fixed array is the workspace."""
+    r = random.Random(4)
+    for _ in range(30000):
+        N, V = _log_int(r, 1, 100000), _log_int(r, 1, 1 << 30)
+        assert lmhead_plan(lib, N, 4096, V, r.random() < 0.5)[7], (N, V)
+    for V in (1, 31, 32, 33, 511, 513, 126464, 152064):
+        for N in range(1, 1300):
+            assert lmhead_plan(lib, N, 64, V, N & 1)[7], (N, V)
+
+
+def test_lmhead_ragged_k_loads_w_like_full_k(lib):
+    """A packed weight past the memory-side cache that is read once is loaded non-temporally whatever
+    d % 64 is (only the hidden rows' loads differ): V = 126464, N = 96 took 191 us cached."""
+    for N in (1, 64, 96, 128, 205):
+        for d in (4096, 4072, 4104, 3000):
+            for V in (64000, 126464, 152064):
+                p = lmhead_plan(lib, N, d, V, True)
+                assert p[4] == (d % 64 != 0) and p[5] == (p[3] == 1 and 2 * V * d > 384000000)
+                assert not lmhead_plan(lib, N, d, V, False)[5]
