@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 
 #include "../../include/asynclane.h"
@@ -181,12 +182,25 @@ static LmLayout lm_layout(int N, int d, int V, bool packed) {
   // 16384 34 us non-temporal, 29 us cached; ragged K too: V = 126464, d = 4072,
   // N = 96 191 us cached, 156 us non-temporal).
   best.var.nt = packed && best.n_nt == 1 && w_bytes > 384.0e6;
+  // Two barriers per K stage (tiles of 512 rows, at most 64 columns) keep loads
+  // in flight across stages.  That wins where the grid leaves compute units
+  // idle, so that each one's own stream counts, and loses a little where the
+  // memory is busy anyway.  MI355X, d = 4096, us per call, one barrier -> two:
+  // packed V = 85000 (167 tiles) 1 row 127 -> 102, 64 rows 136 -> 113; 118000
+  // (231) 145 -> 143, 151 -> 144; 126464 (247) 150 -> 154, 154 -> 155; 200000
+  // (391, two rounds) 270 -> 249; as given 85000 133 -> 122, 142 -> 126; 112000
+  // (219) 1 row 156 -> 158, 32 rows 157 -> 157; 200000 303 -> 284; d = 8192, V =
+  // 128256 (251) 8 rows 352 -> 357, 32 rows 363 -> 356.
+  const double full = (double)best.n_vt * best.n_nt / cus;
+  const double fill = full / std::ceil(full);
+  best.var.split = fill < (packed ? 0.93 : 0.82) || (!packed && N > 16);
   return best;
 }
 
 int al_internal_lmhead_plan(int N, int d, int V, int packed, int32_t* out) {
   const LmLayout L = lm_layout(N, d, V, packed != 0);
-  const int32_t v[8] = {L.ra, L.cbt, L.n_vt, L.n_nt, L.var.ragged, L.var.nt, 0,
+  const int form = lm_stage_form(L.ra, L.cbt);
+  const int32_t v[8] = {L.ra, L.cbt, L.n_vt, L.n_nt, L.var.ragged, L.var.nt, form == 1 || (form == 2 && L.var.split),
                         L.ra != 0 && L.bytes() <= lmhead_workspace_bytes(N, d, V)};
   std::copy(v, v + 8, out);
   return 0;

@@ -20,6 +20,12 @@
 // * One barrier per 64 K elements.  A barrier costs ~250 cycles whatever lies
 //   between (832 cycles of MFMA per 32 elements at 13 fragments took 1390
 //   cycles with a barrier per 32 elements, 68% busy with one per 64).
+// * Tiles of 384 and 512 rows (RA = 6, 8; at most 96 columns) leave LDS for two
+//   stages only.  With one barrier a stage every load has to arrive before
+//   the next is issued; a second barrier (SPLIT) keeps the loads in flight.  At
+//   96 columns it always wins (LLaDA weight packed, N = 77 160 -> 156 us); with
+//   fewer lmhead.hip has the rule and its figures.  RA = 6 fills the chip where RA
+//   = 8 would leave a third of it idle (V = 85000, N = 96: 122 -> 107 us).
 // * Fragments are read one half-stage (32 elements) ahead into a second
 //   register set, so no MFMA waits for an LDS read of its own half-stage.
 // * Wavefronts 0-3 issue all loads.  The SIMD serves its older wavefront
@@ -45,7 +51,7 @@ constexpr int tile_stages(int wb, int hb) {
   return s;
 }
 
-template <int RA, int CBT, bool RAGGED, bool PACKED, bool NT>
+template <int RA, int CBT, bool RAGGED, bool PACKED, bool NT, bool SPLIT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void lmhead_tile_kernel(LmTileParams p) {
   constexpr int CB0 = (CBT + 1) / 2;         // column fragments of wavefronts 0-3
@@ -57,6 +63,7 @@ void lmhead_tile_kernel(LmTileParams p) {
   // (at least two of each).
   constexpr int SH = tile_stages(WB, HB);
   constexpr int SW = (SH + 1) * WB + SH * HB <= 160 * 1024 ? SH + 1 : SH;
+  static_assert(!SPLIT || (SH == 2 && SW == 2), "waits of the two-barrier stage");
   constexpr int COLS = 16 * CBT;
   // Wavefronts 0-3 load: LW pieces (1 KB) of W and LH of the hidden rows
   // each per stage (the last hidden pieces may be loaded twice).
@@ -235,8 +242,12 @@ void lmhead_tile_kernel(LmTileParams p) {
     // stage and the next one is complete: its first half's fragments are
     // read during the second half, and the loads that take the freed
     // buffers are issued (not in a tile's last stage: the epilogue uses the
-    // W buffer first).
+    // hidden buffer first).  SPLIT: with two stages in LDS that order lets
+    // every load arrive before the next is issued; here the next stage need not
+    // be complete at the barrier, so that the freed buffers are refilled while
+    // it is still arriving, and a second barrier follows its wait.
     auto stage = [&](bool refill) {
+      const bool load = LOADER && refill;
       static_for<NC>([&](auto jt) {
         constexpr int j = decltype(jt)::value;
 #pragma unroll
@@ -246,19 +257,20 @@ void lmhead_tile_kernel(LmTileParams p) {
         for (int i = 0; i < RA; ++i) acc[i][j] = mfma16x16x32(a0[i], b0[j], acc[i][j]);
         __builtin_amdgcn_sched_barrier(0);
       });
-      if (LOADER) wait_loads_and_barrier<(SW - SH) * LW + (SH - 2) * L>();
+      if (SPLIT) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else if (LOADER) wait_loads_and_barrier<(SW - SH) * LW + (SH - 2) * L>();
       else wait_loads_and_barrier<0>();
       const int wn = wb + WB == SW * WB ? 0 : wb + WB, hn = hb + HB == SH * HB ? 0 : hb + HB;
       static_for<NC>([&](auto jt) {
         constexpr int j = decltype(jt)::value;
 #pragma unroll
         for (int i = 0; i < RPC; ++i)
-          if (j * RPC + i < RA + NC) read1(a0, b0, ar + wn, br + hn, IntTag<0>{}, j * RPC + i);
+          if (!SPLIT && j * RPC + i < RA + NC) read1(a0, b0, ar + wn, br + hn, IntTag<0>{}, j * RPC + i);
 #pragma unroll
         for (int i = 0; i < RA; ++i) acc[i][j] = mfma16x16x32(a1[i], b1[j], acc[i][j]);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (LOADER && j >= C0) {
-          if (refill)
+          if (load)
             static_for<PPC>([&](auto q) {
               constexpr int x = (j - C0) * PPC + decltype(q)::value;
               if constexpr (x < LH) load_h(IntTag<x>{}, hb);
@@ -266,10 +278,16 @@ void lmhead_tile_kernel(LmTileParams p) {
             });
         }
       });
-      if (LOADER && refill) {
+      if (load) {
         h_advance();
         w_advance();
-        }
+      }
+      if (SPLIT) {
+        if (load) wait_loads_and_barrier<L>();
+        else wait_loads_and_barrier<0>();
+#pragma unroll
+        for (int i = 0; i < RA + NC; ++i) read1(a0, b0, ar + wn, br + hn, IntTag<0>{}, i);
+      }
       if (refill) {
         wb = wn;
         hb = hn;
@@ -360,10 +378,10 @@ void lmhead_tile_kernel(LmTileParams p) {
   // (Every wavefront has waited for its loads: none lands after the end.)
 }
 // ------------------------------------------------------------------ host
-template <int RA, int CBT>
-void launch_lmhead_tile(const LmTileParams& p, LmVariant v, dim3 grid, hipStream_t stream) {
+template <int RA, int CBT, bool SPLIT>
+void launch_form(const LmTileParams& p, LmVariant v, dim3 grid, hipStream_t stream) {
 #define AL_LM_TILE(RG, PK, NTL) \
-  hipLaunchKernelGGL((lmhead_tile_kernel<RA, CBT, RG, PK, NTL>), grid, dim3(512), 0, stream, p)
+  hipLaunchKernelGGL((lmhead_tile_kernel<RA, CBT, RG, PK, NTL, SPLIT>), grid, dim3(512), 0, stream, p)
   if (!v.packed) {
     if (v.ragged) AL_LM_TILE(true, false, false);
     else AL_LM_TILE(false, false, false);
@@ -376,6 +394,14 @@ void launch_lmhead_tile(const LmTileParams& p, LmVariant v, dim3 grid, hipStream
   }
 #undef AL_LM_TILE
 }
+template <int RA, int CBT>
+void launch_lmhead_tile(const LmTileParams& p, LmVariant v, dim3 grid, hipStream_t stream) {
+  constexpr int form = lm_stage_form(RA, CBT);
+  if constexpr (form != 0)
+    if (form == 1 || v.split) return launch_form<RA, CBT, true>(p, v, grid, stream);
+  if constexpr (form != 1) launch_form<RA, CBT, false>(p, v, grid, stream);
+}
+
 #define AL_LM_INSTANCE(RA, CBT) \
   template void launch_lmhead_tile<RA, CBT>(const LmTileParams&, LmVariant, dim3, hipStream_t);
 

@@ -98,3 +98,16 @@ def test_lmhead_ragged_k_loads_w_like_full_k(lib):
                 p = lmhead_plan(lib, N, d, V, True)
                 assert p[4] == (d % 64 != 0) and p[5] == (p[3] == 1 and 2 * V * d > 384000000)
                 assert not lmhead_plan(lib, N, d, V, False)[5]
+
+
+def test_lmhead_few_rows_keep_loads_in_flight(lib):
+    """Tiles of 512 rows have two K stages in LDS.  Where they leave compute units idle (85000 rows of V:
+    167 tiles) one barrier a stage let the W stream drain: 85000 x 4096 packed, 1 row 103 -> 127 us."""
+    for V, N, packed, two in ((85000, 1, True, 1), (85000, 40, True, 1), (85000, 1, False, 1),
+                              (118000, 64, True, 1), (126464, 1, True, 0), (126464, 64, True, 0),
+                              (126464, 77, True, 1), (126464, 77, False, 1), (126464, 1, False, 0),
+                              (126464, 32, False, 1), (200000, 1, True, 1)):
+        p = lmhead_plan(lib, N, 4096, V, packed)
+        assert p[0] >= 6 and p[6] == two, (V, N, packed, p)
+    for N in (77, 96):
+        assert lmhead_plan(lib, N, 4096, 85000, True)[:2] == (6, 6)
