@@ -104,21 +104,26 @@ static __device__ __attribute__((aligned(16))) const unsigned char zero_seg16[16
 // load before any LDS read that follows the builtin; the waits are the
 // kernel's own (wait_loads_and_barrier).  No register is written.
 // LDS address lds + LOFF + OFF, global address sbase + voff + OFF.
+// (m0 holds the LDS address; the compiler warns that it is a reserved register,
+// which it sets afresh for each use of its own.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int LOFF, int OFF, bool NT>
 __device__ __forceinline__ void load_to_lds16(const char* sbase, unsigned voff, unsigned lds) {
   if (NT)
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4 nt"
-                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc");
+                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc", "m0");
   else
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4"
-                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc");
+                 ::"s"(lds), "v"(voff), "s"(sbase), "n"(LOFF), "n"(OFF) : "memory", "scc", "m0");
 }
 // The same with a 64-bit address per lane; LDS address lds + LOFF.
 template <int LOFF>
 __device__ __forceinline__ void load_to_lds16(const char* vaddr, unsigned lds) {
   asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               ::"s"(lds), "v"(vaddr), "n"(LOFF) : "memory", "scc");
+               ::"s"(lds), "v"(vaddr), "n"(LOFF) : "memory", "scc", "m0");
 }
+#pragma clang diagnostic pop
 
 __device__ __forceinline__ const char* uniform_ptr(const char* q) {
   const unsigned long long v = (unsigned long long)q;

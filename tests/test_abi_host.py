@@ -214,3 +214,14 @@ def test_lmhead_workspace_serves_smaller_calls(lib):
     for V in (1, 33, 1024, 9000, 32000, 126464, 152064, 300001, 1 << 24):
         sizes = [lib.lmhead_confidence_workspace_size(n, 4096, V) for n in range(1, 1300)]
         assert all(b >= a > 0 for a, b in zip(sizes, sizes[1:])), V
+
+
+def test_inline_asm_names_m0_as_clobbered():
+    """Inline asm that sets m0 (the LDS address of a direct load) says so to the compiler."""
+    found = 0
+    for f in glob.glob(os.path.join(ROOT, "paper_2606_08411_amd", "csrc", "*")):
+        for stmt in re.findall(r"\basm\b[^;]*;", open(f).read()):
+            if re.search(r"\bm0,", stmt):
+                found += 1
+                assert '"m0"' in stmt.rsplit(":", 1)[1], stmt
+    assert found == 3
