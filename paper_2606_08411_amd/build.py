@@ -17,7 +17,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libasynclane.so")
 FAST = os.path.join(PKG, "_fast.so")   # CPython module (csrc/fast_call.cpp)
 SOURCES = (["abi.cpp", "scheduler.cpp", "lane_attn.hip", "lmhead.hip", "select_unmask.hip"] +
-           [f"lmhead_tile_{g}.hip" for g in "abcdefghi"])
+           [f"lmhead_tile_{g}.hip" for g in "abcdefghij"])
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

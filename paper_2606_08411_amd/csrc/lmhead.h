@@ -51,8 +51,8 @@ struct LmTileParams {
 // most 96 columns on large vocabularies, where the W stream is the bound.  The
 // sources lmhead_tile_*.hip hold a few each.
 #define AL_LM_INSTANCES(X)                                                                  \
-  X(1, 2) X(1, 4) X(1, 6) X(1, 8) X(1, 10) X(1, 13) X(1, 16)                                \
-  X(2, 2) X(2, 4) X(2, 6) X(2, 8) X(2, 10) X(2, 13) X(2, 16)                                \
+  X(1, 2) X(1, 4) X(1, 6) X(1, 10)                                                         \
+  X(2, 2) X(2, 4) X(2, 6) X(2, 8) X(2, 10) X(2, 13)                                         \
   X(4, 2) X(4, 4) X(4, 6) X(4, 8) X(4, 9) X(4, 10) X(4, 11) X(4, 12) X(4, 13) X(4, 14)      \
   X(4, 15) X(4, 16)                                                                         \
   X(5, 4) X(5, 6) X(5, 8) X(5, 9) X(5, 10) X(5, 11) X(5, 12) X(5, 13)                       \

@@ -104,11 +104,22 @@ constexpr struct {
 #undef AL_LM_X
 };
 
-// Workspace bytes.  The bound of the 256- and 512-row vocabulary tiles (rows
-// to 32 columns, tiles to a multiple of the CU count) decides which calls
-// the fixed array of lmhead_confidence_noalloc takes; smaller tiles for small
+// Workspace bytes.  The bound is a tiling by 256 or 512 vocabulary rows x nf <= 7
+// fragments of 32 columns, with the tiles rounded up to a multiple of the CU
+// count: callers keep workspaces of these sizes, and they decide which calls
+// the fixed array of lmhead_confidence_noalloc takes.  Smaller tiles for small
 // vocabularies may take more, up to that array's size.  Both grow with N, so
-// a workspace made for N rows serves every smaller call.
+// a workspace made for N rows serves every smaller call.  Some layout always
+// fits: the instance of that tiling's own rows and columns, for each nf.
+constexpr bool lm_bound_is_built() {
+  for (int nf = 1; nf <= 7; ++nf) {
+    bool found = false;
+    for (const auto& in : kLmInstances) found |= in.ra == (nf <= 3 ? 8 : 4) && in.cbt == 2 * nf;
+    if (!found) return false;
+  }
+  return true;
+}
+static_assert(lm_bound_is_built(), "an instance for every column count of the workspace bound");
 static size_t lm_tile_bound(int N, int V, bool packed, int cus) {
   const int frags = (N + 31) / 32;
   const bool multi = packed && frags > 7;

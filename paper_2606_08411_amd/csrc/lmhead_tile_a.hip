@@ -6,11 +6,9 @@ namespace al {
 AL_LM_INSTANCE(1, 2)
 AL_LM_INSTANCE(1, 4)
 AL_LM_INSTANCE(1, 6)
-AL_LM_INSTANCE(1, 8)
 AL_LM_INSTANCE(1, 10)
-AL_LM_INSTANCE(1, 13)
-AL_LM_INSTANCE(1, 16)
 AL_LM_INSTANCE(2, 2)
 AL_LM_INSTANCE(2, 4)
+AL_LM_INSTANCE(2, 6)
 
 }  // namespace al

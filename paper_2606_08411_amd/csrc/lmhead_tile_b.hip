@@ -3,10 +3,10 @@
 
 namespace al {
 
-AL_LM_INSTANCE(2, 6)
 AL_LM_INSTANCE(2, 8)
 AL_LM_INSTANCE(2, 10)
 AL_LM_INSTANCE(2, 13)
-AL_LM_INSTANCE(2, 16)
+AL_LM_INSTANCE(4, 2)
+AL_LM_INSTANCE(4, 4)
 
 }  // namespace al

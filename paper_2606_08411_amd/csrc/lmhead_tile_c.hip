@@ -3,10 +3,9 @@
 
 namespace al {
 
-AL_LM_INSTANCE(4, 2)
-AL_LM_INSTANCE(4, 4)
 AL_LM_INSTANCE(4, 6)
 AL_LM_INSTANCE(4, 8)
 AL_LM_INSTANCE(4, 9)
+AL_LM_INSTANCE(4, 10)
 
 }  // namespace al

@@ -3,7 +3,6 @@
 
 namespace al {
 
-AL_LM_INSTANCE(4, 10)
 AL_LM_INSTANCE(4, 11)
 AL_LM_INSTANCE(4, 12)
 

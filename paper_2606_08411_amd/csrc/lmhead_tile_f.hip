@@ -5,7 +5,5 @@ namespace al {
 
 AL_LM_INSTANCE(4, 15)
 AL_LM_INSTANCE(4, 16)
-AL_LM_INSTANCE(6, 6)
-AL_LM_INSTANCE(8, 2)
 
 }  // namespace al

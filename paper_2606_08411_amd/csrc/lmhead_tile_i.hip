@@ -3,7 +3,7 @@
 
 namespace al {
 
-AL_LM_INSTANCE(8, 4)
-AL_LM_INSTANCE(8, 6)
+AL_LM_INSTANCE(6, 6)
+AL_LM_INSTANCE(8, 2)
 
 }  // namespace al

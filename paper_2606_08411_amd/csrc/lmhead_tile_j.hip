@@ -1,0 +1,9 @@
+// Instances of the LM-head tile kernel (several sources, compiled in parallel).
+#include "lmhead_tile.h"
+
+namespace al {
+
+AL_LM_INSTANCE(8, 4)
+AL_LM_INSTANCE(8, 6)
+
+}  // namespace al

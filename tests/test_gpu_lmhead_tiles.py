@@ -1,7 +1,7 @@
-"""The LM-head tile kernel at the edges of its tiles: every column-tile width,
-one and several column tiles, every vocabulary-tile height, one and several
-tiles per workgroup, K ragged against the 64-element stages, vocabularies
-ragged against the 32-row units and the 8-row pieces of W as given.
+"""The LM-head tile kernel at the edges of its tiles: row counts around each column-tile width,
+one and several column tiles, one and several tiles per workgroup, K ragged against the 64-element
+stages, vocabularies ragged against the 32-row units and the 8-row pieces of W as given, down to one
+row, one token and 8 elements.  (test_gpu_lmhead_instances.py runs every built instance.)
 
 Against the fp64 oracle.  Tolerance: a logit is an fp32 sum of d <= 320 products
 (|h| < 25, |w| ~ 1/sqrt(d), |z| up to ~30; rounding error about

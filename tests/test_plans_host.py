@@ -7,6 +7,7 @@ import random
 import pytest
 
 import test_gpu_attention_tiles
+import test_gpu_lmhead_instances
 
 
 @pytest.fixture(scope="module")
@@ -73,6 +74,11 @@ def lmhead_plan(lib, N, d, V, packed):
     return tuple(out)
 
 
+def _lmhead_kind(plan):
+    """The kernel that runs: (RA, CBT, two barriers, ragged, non-temporal)."""
+    return plan[0], plan[1], plan[6], plan[4], plan[5]
+
+
 def _log_int(r, lo, hi):
     return int(round(math.exp(r.uniform(math.log(lo), math.log(hi)))))
 
@@ -111,3 +117,35 @@ def test_lmhead_few_rows_keep_loads_in_flight(lib):
         assert p[0] >= 6 and p[6] == two, (V, N, packed, p)
     for N in (77, 96):
         assert lmhead_plan(lib, N, 4096, 85000, True)[:2] == (6, 6)
+
+
+def test_lmhead_cases_reach_every_instance(lib):
+    """Every built (RA, CBT) in each of its stage forms, ragged and not, packed and as given, with one
+    tile a workgroup and (from 256 rows of V a tile on) several; every non-temporal kernel."""
+    T = test_gpu_lmhead_instances
+    pairs = (ctypes.c_int32 * 400)()
+    built = {(pairs[2 * i], pairs[2 * i + 1])
+             for i in range(lib.al_internal_lmhead_instances(pairs, 200))}
+    tested, several, nt = set(), set(), set()
+    for N, d, V in T.SIZES:
+        for packed in (False, True):
+            p = lmhead_plan(lib, N, d, V, packed)
+            (several if p[2] * p[3] > 256 else tested).add((packed,) + _lmhead_kind(p))
+    for N, d, V in T.NT_SIZES:
+        p = lmhead_plan(lib, N, d, V, True)
+        assert p[5]
+        nt.add(_lmhead_kind(p))
+    assert {k[1:3] for k in tested} == built
+    r = random.Random(6)
+    for _ in range(60000):   # what the sizes in use reach
+        d = 8 * _log_int(r, 1, 2048)
+        N, V, packed = _log_int(r, 1, 1200), _log_int(r, 64, 260000), r.random() < 0.6
+        p = lmhead_plan(lib, N, d, V, packed)
+        k = (packed,) + _lmhead_kind(p)
+        if p[5]:
+            assert k[1:] in nt, (N, d, V, k)
+        else:
+            k = k[:5] + (0,)
+            assert k in tested, (N, d, V, k)
+            if p[2] * p[3] > 256 and p[0] >= 4:
+                assert k in several, (N, d, V, k)
