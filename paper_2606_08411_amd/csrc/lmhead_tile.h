@@ -63,7 +63,8 @@ void lmhead_tile_kernel(LmTileParams p) {
   // (at least two of each).
   constexpr int SH = tile_stages(WB, HB);
   constexpr int SW = (SH + 1) * WB + SH * HB <= 160 * 1024 ? SH + 1 : SH;
-  static_assert(!SPLIT || (SH == 2 && SW == 2), "waits of the two-barrier stage");
+  constexpr bool TWO = SH == 2 && SW == 2;
+  static_assert(!SPLIT || TWO, "waits of the two-barrier stage");
   constexpr int COLS = 16 * CBT;
   // Wavefronts 0-3 load: LW pieces (1 KB) of W and LH of the hidden rows
   // each per stage (the last hidden pieces may be loaded twice).
@@ -98,6 +99,7 @@ void lmhead_tile_kernel(LmTileParams p) {
   const char* hp = nullptr;
   unsigned hoff[LH];
   int ht = t0, hleft = 0;
+  int todo = TWO ? (tend - t0 + slots - 1) / slots * nst - SH : 1;
   // W as given is walked in a rotated K order, one start per group of eight
   // neighbouring tiles: workgroups in step would otherwise all read one
   // column offset of W at a time, and how those requests spread over the HBM
@@ -161,8 +163,11 @@ void lmhead_tile_kernel(LmTileParams p) {
       load_to_lds16<0, 0, false>(uniform_ptr(hp), hoff[J], lds);
     }
   };
-  // To the next stage; past the last tile the loads go on with a tile whose
+  // To the next stage.  Past the last tile the loads go on with a tile whose
   // data nobody reads, so that the number in flight stays what the waits say.
+  // With two stages in LDS (TWO) every wait but one is for all loads, and they end:
+  // todo counts the stages still to load.  (LLaDA weight packed, N = 77: 1.050
+  // GB fetched per call -> 1.042.)
   auto w_advance = [&]() {
     wp += PACKED ? (size_t)p.n_hg * 4096 : (size_t)128;
     if (!PACKED && ++wk == nst) {
@@ -247,7 +252,7 @@ void lmhead_tile_kernel(LmTileParams p) {
     // be complete at the barrier, so that the freed buffers are refilled while
     // it is still arriving, and a second barrier follows its wait.
     auto stage = [&](bool refill) {
-      const bool load = LOADER && refill;
+      const bool load = LOADER && refill && (!TWO || todo > 0);
       static_for<NC>([&](auto jt) {
         constexpr int j = decltype(jt)::value;
 #pragma unroll
@@ -281,6 +286,7 @@ void lmhead_tile_kernel(LmTileParams p) {
       if (load) {
         h_advance();
         w_advance();
+        if (TWO) --todo;
       }
       if (SPLIT) {
         if (load) wait_loads_and_barrier<L>();
@@ -362,11 +368,12 @@ void lmhead_tile_kernel(LmTileParams p) {
       // The stores drain here so that the loop's load counts hold.
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
       if (t + slots < tend) {
-        if (LOADER) {
+        if (LOADER && (!TWO || todo > 0)) {
           static_for<LH>([&](auto j) { load_h(j, hb); });
           static_for<LW>([&](auto j) { load_w(j, wb); });
           h_advance();
           w_advance();
+          if (TWO) --todo;
         }
         wb = wb + WB == SW * WB ? 0 : wb + WB;
         hb = hb + HB == SH * HB ? 0 : hb + HB;

@@ -51,6 +51,16 @@ def test_traffic_record_matches_layout_and_code():
     assert bench.measured_traffic("no_such_workload", "packed") is None
 
 
+def test_traffic_record_reads_w_once():
+    """The recorded LLaDA-shape call fetches W once, the scored hidden rows once per L2 (8 XCDs) and
+    its partials (247 vocabulary tiles x 96 columns x 16 bytes, written and read), within 0.2%: no
+    stage of W is loaded that nobody uses (16 MB, 1.5%, if each workgroup loads one past its last)."""
+    with open(os.path.join(ROOT, "profiles", "lmhead_confidence_llada_pmc.json")) as f:
+        rec = json.load(f)
+    V, d, N = 126464, 4096, 77
+    assert rec["hbm_bytes_per_launch"] < 1.002 * (2 * V * d + 8 * 2 * N * d + 2 * 247 * 96 * 16)
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=300, cwd=ROOT)
