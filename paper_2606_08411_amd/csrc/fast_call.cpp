@@ -95,7 +95,8 @@ void host_array(PyObject* o, T* out, Py_ssize_t n) {
     for (Py_ssize_t i = 0; i < n; ++i) out[i] = (T)to_int(PySequence_Fast_GET_ITEM(o, i));
     return;
   }
-  if (!PyObject_CheckBuffer(o) || THPVariable_Check(o)) throw Skip{};
+  // (bytes have a buffer too, but numpy takes them for text and refuses them)
+  if (!PyObject_CheckBuffer(o) || PyBytes_Check(o) || THPVariable_Check(o)) throw Skip{};
   Py_buffer b;
   if (PyObject_GetBuffer(o, &b, PyBUF_FORMAT | PyBUF_ND | PyBUF_C_CONTIGUOUS) != 0) {
     PyErr_Clear();
@@ -222,14 +223,14 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t na) {
       throw Skip{};
     }
     if (L > AL_MAX_LANES) throw Skip{};
-    if (L > 0) host_array(a[5], parent, L);
+    host_array(a[5], parent, L);
     int64_t n_ref = 0, Hq = 0;
     int B = 16;
     void *qp = nullptr, *klp = nullptr, *vlp = nullptr;
     at::Tensor mo, ml, mor, mlr;
     void *op = nullptr, *lp = nullptr, *orp = nullptr, *lrp = nullptr;
     if (ri) {
-      if (ri->dim() != 1) throw Skip{};
+      if (ri->dim() != 1 || ri->size(0) == 0) throw Skip{};
       n_ref = ri->size(0);
     }
     if (L > 0) {

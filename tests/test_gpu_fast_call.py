@@ -1,7 +1,7 @@
 """The native marshalling of the decode-step calls against the Python checks:
 every accepted form of the arguments gives the same results both ways, what
 one refuses the other refuses with the same message, and argument forms the
-native path does not know fall through to the Python checks."""
+native path does not know fall through to the Python checks.  Each form states which of these it is."""
 import numpy as np
 import pytest
 import torch
@@ -19,12 +19,29 @@ class _Decline:
         return lambda *a: None
 
 
-def _both(monkeypatch, call):
-    """Outcome of call() natively marshalled and through the Python checks."""
+class _Record:
+    """The native module; how = what it made of the last call: "native", "declined" or "raised"."""
+
+    def __init__(self, fast):
+        self.fast, self.how = fast, None
+
+    def __getattr__(self, name):
+        def call(*a):
+            self.how = "raised"
+            r = getattr(self.fast, name)(*a)
+            self.how = "declined" if r is None else "native"
+            return r
+        return call
+
+
+def _both(monkeypatch, call, how="native"):
+    """Outcome of call() natively marshalled and through the Python checks; how: what the native
+    module makes of it (declined: both outcomes come from the Python checks)."""
     from paper_2606_08411_amd import _lib
     _lib.library()
     got = []
-    for fast in (_lib._fast, _Decline()):
+    rec = _Record(_lib._fast)
+    for fast in (rec, _Decline()):
         with monkeypatch.context() as m:
             m.setattr(_lib, "_fast", fast)
             try:
@@ -34,6 +51,7 @@ def _both(monkeypatch, call):
                 got.append([None if x is None else x.clone() for x in r])
             except Exception as e:   # noqa: BLE001 - compared below
                 got.append((type(e), str(e)))
+    assert rec.how == how
     return got
 
 
@@ -60,6 +78,10 @@ def _attn_args(n_ref=0, L=3):
     return a
 
 
+class _Subclass(torch.Tensor):
+    pass
+
+
 ATTN = {
     "plain": lambda a: a,
     "list": lambda a: dict(a, parent=[int(x) for x in a["parent"]]),
@@ -70,7 +92,8 @@ ATTN = {
     "no lse": lambda a: dict(a, want_lse=False),
     "scale": lambda a: dict(a, scale=np.float64(0.2)),
     "outputs": lambda a: dict(a, o=torch.empty_like(a["q"])),
-    "subclass": lambda a: dict(a, q=torch.nn.Parameter(a["q"], requires_grad=False)),
+    "parameter": lambda a: dict(a, q=torch.nn.Parameter(a["q"], requires_grad=False)),
+    "subclass": lambda a: dict(a, q=a["q"].as_subclass(_Subclass)),
     "bad tree": lambda a: dict(a, parent=[0, 0, 0]),
     "short parent": lambda a: dict(a, parent=a["parent"][:2]),
     "dtype": lambda a: dict(a, q=a["q"].float()),
@@ -80,7 +103,15 @@ ATTN = {
     "missing": lambda a: dict(a, v_lane=None),
     "small workspace": lambda a: dict(a, workspace=torch.empty(16, dtype=torch.uint8, device="cuda")),
     "no workspace tensor": lambda a: dict(a, workspace=7),
+    "empty host index": lambda a: a if "q_ref" in a else dict(
+        a, refresh_idx=torch.empty(0, dtype=torch.int32)),
+    "index dtype": lambda a: dict(a, refresh_idx=a["refresh_idx"].long()) if "q_ref" in a else a,
 }
+# What the native module makes of a form, where not "native".
+ATTN_HOW = dict.fromkeys(
+    ("int64", "strided", "numpy B", "subclass", "short parent", "dtype", "shape", "layout", "cpu",
+     "missing", "no workspace tensor"), "declined")
+ATTN_HOW.update({"bad tree": "raised", ("empty host index", 0): "declined", ("index dtype", 7): "declined"})
 
 
 @pytest.mark.parametrize("form", ATTN)
@@ -88,7 +119,8 @@ ATTN = {
 def test_attention_forms(form, n_ref, monkeypatch):
     import paper_2606_08411_amd as al
     a = ATTN[form](_attn_args(n_ref))
-    _same(_both(monkeypatch, lambda: al.lane_attn_forward(**a)))
+    how = ATTN_HOW.get((form, n_ref), ATTN_HOW.get(form, "native"))
+    _same(_both(monkeypatch, lambda: al.lane_attn_forward(**a), how))
 
 
 def test_attention_refresh_only(monkeypatch):
@@ -96,6 +128,17 @@ def test_attention_refresh_only(monkeypatch):
     a = _attn_args(7)
     a.update(q=None, k_lane=None, v_lane=None, parent=[])
     _same(_both(monkeypatch, lambda: al.lane_attn_forward(**a)))
+
+
+@pytest.mark.parametrize("parent,how", [
+    ([], "native"), ((), "native"), (np.zeros(0, np.int32), "native"), (np.zeros(0), "declined"),
+    ({}, "declined"), ("", "declined"), (b"", "declined"), (np.zeros((0, 3), np.int32), "declined")], ids=repr)
+def test_no_lanes_forms(parent, how, monkeypatch):
+    """Without lanes the parent is still an empty list of ints or refused."""
+    import paper_2606_08411_amd as al
+    a = _attn_args(7)
+    a.update(q=None, k_lane=None, v_lane=None, parent=parent)
+    _same(_both(monkeypatch, lambda: al.lane_attn_forward(**a), how))
 
 
 LM = {
@@ -111,6 +154,8 @@ LM = {
     "numpy eos": lambda a: dict(a, eos_id=np.int32(3)),
     "hidden": lambda a: dict(a, hidden=a["hidden"][:, ::2]),
 }
+LM_HOW = dict.fromkeys(("short outputs", "no rows", "row dtype", "numpy eos", "hidden"), "declined")
+LM_HOW["eos"] = "raised"
 
 
 @pytest.mark.parametrize("packed", [False, True], ids=["plain", "packed"])
@@ -124,9 +169,10 @@ def test_lmhead_forms(form, packed, monkeypatch):
     W = bf(700, 64)
     if packed:
         Wp = al.lmhead_pack_weight(W)
-        _same(_both(monkeypatch, lambda: al.lmhead_confidence_packed(W_packed=Wp, V=700, **a)))
+        call = lambda: al.lmhead_confidence_packed(W_packed=Wp, V=700, **a)
     else:
-        _same(_both(monkeypatch, lambda: al.lmhead_confidence(W=W, **a)))
+        call = lambda: al.lmhead_confidence(W=W, **a)
+    _same(_both(monkeypatch, call, LM_HOW.get(form, "native")))
 
 
 SEL = {
@@ -136,7 +182,12 @@ SEL = {
     "id array": dict(delim_ids=np.array([5, 6])), "many ids": dict(delim_ids=tuple(range(17))),
     "role list": dict(role=[0, 1]), "role value": dict(role=np.array([0, 9], np.uint8)),
     "nan": dict(tau=float("nan")), "t_lane": dict(t_lane=(3, 4)), "short": dict(t_lane=(3,)),
+    "role bytes": dict(role=b"\0\1"), "role bytearray": dict(role=bytearray(b"\0\1")),
+    "t_lane bytes": dict(t_lane=b"\0\1"), "int64 t_lane": dict(t_lane=np.array([3, 4])),
 }
+SEL_HOW = dict.fromkeys(("id array", "many ids", "role list", "short", "role bytes", "t_lane bytes",
+                         "int64 t_lane"), "declined")
+SEL_HOW.update(dict.fromkeys(("topk without k", "role value", "nan"), "raised"))
 
 
 @pytest.mark.parametrize("form", SEL)
@@ -156,7 +207,7 @@ def test_select_forms(form, monkeypatch):
         assert r is out
         return dict(r, tok=tok, msk=msk)
 
-    _same(_both(monkeypatch, call))
+    _same(_both(monkeypatch, call, SEL_HOW.get(form, "native")))
 
 
 def test_outputs_given_are_returned():
@@ -172,6 +223,6 @@ def test_capture_without_workspace_is_refused(monkeypatch):
     W = torch.zeros((700, 64), dtype=torch.bfloat16, device="cuda")
     h = torch.zeros((8, 64), dtype=torch.bfloat16, device="cuda")
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
-    _same(_both(monkeypatch, lambda: al.lmhead_confidence(h, W)))
+    _same(_both(monkeypatch, lambda: al.lmhead_confidence(h, W), "raised"))
     with pytest.raises(al.AsyncLaneError, match="being captured"):
         al.lmhead_confidence(h, W)
