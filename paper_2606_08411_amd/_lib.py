@@ -4,8 +4,9 @@ the three calls of a decode step natively (~16 us of Python per call before).
 
 Argument marshalling only: every step of the decode-step hot path runs in the
 library's HIP kernels.  PyTorch supplies device memory and the current HIP
-stream.  There is no fallback: when the library is missing or a call fails,
-an exception is raised.
+stream.  There is no fallback for the library: when it is missing or a call
+fails, an exception is raised.  The native module is bound to one torch build;
+without it a warning is given and every call is marshalled in Python.
 """
 from __future__ import annotations
 
@@ -14,6 +15,7 @@ import importlib.machinery
 import importlib.util
 import os
 import threading
+import warnings
 
 import numpy as np
 import torch
@@ -74,27 +76,46 @@ class AsyncLaneError(RuntimeError):
     pass
 
 
+class _NoFast:
+    """Stands in for the native module: declines every call."""
+
+    @staticmethod
+    def attn(*args):
+        return None
+
+    lmhead = select = attn
+
+
+def _load_fast(lib):
+    """The native marshalling module, or _NoFast when it is not built or not for this torch."""
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_fast", FAST_PATH)
+        fast = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fast", loader))
+        loader.exec_module(fast)
+    except (ImportError, OSError) as e:
+        warnings.warn(f"{FAST_PATH} does not load ({e}): calls are marshalled in Python, ~11 us more "
+                      "each; build it with `python -m paper_2606_08411_amd.build`")
+        return _NoFast
+    fast.init({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _SIGNATURES},
+              _check, _workspace, _raw_stream or _slow_raw_stream)
+    return fast
+
+
 def library() -> ctypes.CDLL:
-    """Load libasynclane.so and _fast.so (raises when they have not been built)."""
+    """Load libasynclane.so (raises when it has not been built) and _fast.so."""
     global _lib, _fast
     with _lock:
         if _lib is None:
-            for path in (LIB_PATH, FAST_PATH):
-                if not os.path.exists(path):
-                    raise AsyncLaneError(
-                        f"{path} is missing: build it with "
-                        "`python -m paper_2606_08411_amd.build` (hipcc, gfx950)")
+            if not os.path.exists(LIB_PATH):
+                raise AsyncLaneError(
+                    f"{LIB_PATH} is missing: build it with "
+                    "`python -m paper_2606_08411_amd.build` (hipcc, gfx950)")
             lib = ctypes.CDLL(LIB_PATH)
             for name, (res, args) in _SIGNATURES.items():
                 fn = getattr(lib, name)
                 fn.restype = res
                 fn.argtypes = args
-            loader = importlib.machinery.ExtensionFileLoader("_fast", FAST_PATH)
-            fast = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fast", loader))
-            loader.exec_module(fast)
-            fast.init({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _SIGNATURES},
-                      _check, _workspace, _raw_stream or _slow_raw_stream)
-            _fast = fast   # before _lib: callers that see _lib use _fast
+            _fast = _load_fast(lib)   # before _lib: callers that see _lib use _fast
             _lib = lib
     return _lib
 

@@ -57,14 +57,15 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(BUILD, os.path.splitext(s)[0] + ".o")
         objs.append(obj)
         cmds.append([HIPCC, "-x", "hip", "-c", os.path.join(CSRC, s), "-o", obj] + FLAGS)
-    cmds.append(_fast_command(FAST + ".tmp"))
-    with ThreadPoolExecutor(min(len(cmds), 8)) as ex:
+    with ThreadPoolExecutor(8) as ex:
+        fast = ex.submit(lambda: _run(_fast_command(FAST + ".tmp")))
         for err in ex.map(_run, cmds):
             if verbose and err.strip():
                 print(err, file=sys.stderr)
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    fast.result()   # (the library is usable without the module)
     os.replace(FAST + ".tmp", FAST)
     return LIB
 

@@ -194,3 +194,32 @@ def test_declining_natively_is_cheap():
             _lib._fast.lmhead(*args)
         best = min(best, (time.perf_counter() - t) / 500)
     assert best < 1e-6
+
+
+@pytest.mark.parametrize("content", [None, b"not a shared object"], ids=["missing", "unloadable"])
+def test_the_library_loads_without_the_native_module(content, monkeypatch, tmp_path):
+    """A build without the module, or a torch that it was not built for, marshals in Python."""
+    from paper_2606_08411_amd import _lib
+    path = tmp_path / "_fast.so"
+    if content:
+        path.write_bytes(content)
+    for name, value in (("FAST_PATH", str(path)), ("_lib", None), ("_fast", None)):
+        monkeypatch.setattr(_lib, name, value)
+    with pytest.warns(UserWarning, match="marshalled in Python"):
+        _lib.library()
+    assert al.lmhead_confidence_workspace_size(77, 4096, 126464) > 0
+    with pytest.raises(AsyncLaneError, match="device tensor expected"):
+        al.lane_attn_forward(**_attn_args())
+    with pytest.raises(AsyncLaneError, match="q: dtype"):
+        al.lane_attn_forward(**dict(_attn_args(), q=torch.zeros(32, 4, 64)))
+
+
+def test_build_keeps_the_library_when_the_module_fails(monkeypatch, tmp_path):
+    from paper_2606_08411_amd import build
+    for name, value in (("SOURCES", ["scheduler.cpp"]), ("BUILD", str(tmp_path)),
+                        ("LIB", str(tmp_path / "lib.so")), ("FAST", str(tmp_path / "_fast.so")),
+                        ("_fast_command", lambda out: ["false"])):
+        monkeypatch.setattr(build, name, value)
+    with pytest.raises(RuntimeError, match="command failed: false"):
+        build.build()
+    assert (tmp_path / "lib.so").exists() and not (tmp_path / "_fast.so").exists()
