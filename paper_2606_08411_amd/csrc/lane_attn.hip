@@ -1052,6 +1052,9 @@ static hipError_t run_pass(const AttnParams& base, const PassShape& s, const Att
 // round; neighbours in this order share most of their ancestors.  (32 random
 // lanes of 64 to depth 8, four to a workgroup: at most 11 blocks against 16 in
 // index order; 16 of 32 to depth 6, eight to a workgroup: 12 against 15.)
+// Index order -> this, us per call (MI355X, random trees): 32 of 64 over 4096 rows x 32
+// heads 156.6 -> 150.3, 32 of 32 over 700 31.3 -> 29.1, 64 of 64 over 64 45.4 -> 38.0, 16 of
+// 32 over 2048 37.0 -> 36.7, 12 of 64 over 1500 21.8 -> 22.3; chains the same.
 // Lane i's parent is the highest of its ancestors (parents come first); any
 // order is correct.
 static void dfs_order(const unsigned long long* vis, int L, unsigned* order) {
