@@ -209,9 +209,9 @@ int lmhead_confidence(const al_bf16* hidden, int n_rows,
  * lmhead_confidence_packed: arguments, results and errors of
  * lmhead_confidence with W_packed in place of W; the workspace size is
  * lmhead_confidence_workspace_size(N, d, V).  Results equal
- * lmhead_confidence's within rounding (the vocabulary is tiled in 32-row
- * units, so the fp32 sums are grouped and ordered differently); argmax
- * ties still go to the lowest id.
+ * lmhead_confidence's within rounding (W as given is walked in a rotated K
+ * order, so the fp32 sums are ordered differently); argmax ties still go to
+ * the lowest id.
  * ------------------------------------------------------------------------ */
 size_t lmhead_packed_weight_size(int d, int V);
 

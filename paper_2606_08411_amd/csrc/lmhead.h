@@ -55,7 +55,7 @@ struct LmTileParams {
   X(2, 2) X(2, 4) X(2, 6) X(2, 8) X(2, 10) X(2, 13)                                         \
   X(4, 2) X(4, 4) X(4, 6) X(4, 8) X(4, 9) X(4, 10) X(4, 11) X(4, 12) X(4, 13) X(4, 14)      \
   X(4, 15) X(4, 16)                                                                         \
-  X(5, 4) X(5, 6) X(5, 8) X(5, 9) X(5, 10) X(5, 11) X(5, 12) X(5, 13)                       \
+  X(5, 2) X(5, 4) X(5, 6) X(5, 8) X(5, 9) X(5, 10) X(5, 11) X(5, 12) X(5, 13)               \
   X(6, 6) X(8, 2) X(8, 4) X(8, 6)
 
 // Stage forms of an instance: 0 one barrier per K stage, 1 two (SPLIT), 2 both

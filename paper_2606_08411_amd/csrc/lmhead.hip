@@ -174,6 +174,9 @@ static LmLayout lm_layout(int N, int d, int V, bool packed) {
     if (c.bytes() > limit) continue;
     const long long tiles = (long long)c.n_vt * c.n_nt;
     const double rounds = (double)((tiles + cus - 1) / cus);
+    // 320 rows x 32 columns: up to two rounds (V = 140000 198 -> 169 us, 81900 109 ->
+    // 105, 1 row packed); past them 512-row tiles read better (V = 330000 446 us, 407).
+    if (c.ra == 5 && c.cbt == 2 && rounds > 2) continue;
     const double busy = std::min(1.0, (double)tiles / cus);
     const bool two = 3 * c.ra * 8192 + 2 * c.cbt * 2048 > 160 * 1024;
     const double stage = 1e-3 * (91 + 36 * c.ra + 13 * c.cbt + 8.8 * c.ra * c.cbt) *

@@ -3,6 +3,7 @@
 
 namespace al {
 
+AL_LM_INSTANCE(5, 2)
 AL_LM_INSTANCE(6, 6)
 AL_LM_INSTANCE(8, 2)
 

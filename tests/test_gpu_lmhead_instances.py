@@ -19,7 +19,7 @@ CASES = [  # N, V at d = 576 and, ragged, V - 3 at d = 568
     (195, 16480), (1, 33000), (1, 131200), (33, 33040), (33, 163880), (67, 33000), (211, 20600), (100, 82400),
     (133, 33160), (131, 84200), (292, 18280), (294, 43760), (326, 21920), (165, 83400), (180, 41400),
     (180, 82400), (197, 36200), (197, 83400), (213, 41160), (213, 82200), (229, 41400), (229, 82200), (487, 21880),
-    (490, 43920), (1, 65680), (40, 133400), (518, 10880), (265, 43760), (197, 33240), (330, 43840), (389, 22000),
+    (490, 43920), (1, 65680), (40, 65680), (1, 133400), (40, 133400), (1, 178000), (518, 10880), (265, 43760), (197, 33240), (330, 43840), (389, 22000),
     (390, 43680), (440, 22800), (580, 33040), (326, 33200), (328, 65800), (545, 21920), (356, 66040), (785, 16560),
     (398, 65800), (70, 82400), (70, 166200), (1, 107200), (1, 122400), (1, 214800), (1, 244000), (2, 82400),
     (2, 197000), (40, 123000), (40, 246000), (40, 82400), (70, 98600), (270, 83200),
@@ -28,7 +28,7 @@ SIZES = [(N, d, v) for N, V in CASES for d, v in ((576, V), (568, V - 3))] + [
     (70, 1152, 166320), (77, 1144, 166317), (34, 64, 204144), (34, 40, 204141)]
 NT_CASES = [  # N, V at d = 4096 and, ragged, V - 3 at d = 4072
     (1, 47520), (40, 47520), (70, 47520), (100, 47520), (135, 47600), (150, 48000), (165, 48400), (180, 47800),
-    (200, 47800), (213, 47800), (230, 47600), (245, 48200), (1, 65800), (70, 66000), (100, 65900), (135, 66200),
+    (200, 47800), (213, 47800), (230, 47600), (245, 48200), (1, 65800), (40, 65800), (70, 66000), (100, 65900), (135, 66200),
     (150, 65900), (165, 65900), (180, 66200), (200, 65900), (70, 82400), (2, 122400), (2, 82400), (40, 122600),
     (40, 82400), (70, 99200),
 ]

@@ -119,6 +119,17 @@ def test_lmhead_few_rows_keep_loads_in_flight(lib):
         assert lmhead_plan(lib, N, 4096, 85000, True)[:2] == (6, 6)
 
 
+def test_lmhead_narrow_tiles_for_few_rows(lib):
+    """32 rows or fewer do not compute 64 columns where 320-row tiles fill one or two rounds
+    (V = 134000 as given, 1 row: 209 us before the tile kernel, 219 with 64 columns, 189 with 32)."""
+    for N in (1, 32):
+        for V in (66000, 81900, 134000, 140000, 152064, 163000):
+            for packed in (False, True):
+                assert lmhead_plan(lib, N, 4096, V, packed)[:2] == (5, 2), (N, V)
+        for V in (200000, 256000, 330000):
+            assert lmhead_plan(lib, N, 4096, V, True)[:2] == (8, 2), (N, V)
+
+
 def test_lmhead_cases_reach_every_instance(lib):
     """Every built (RA, CBT) in each of its stage forms, ragged and not, packed and as given, with one
     tile a workgroup and (from 256 rows of V a tile on) several; every non-temporal kernel."""
