@@ -62,9 +62,9 @@ size_t lane_attn_workspace_size(int L, int B, int P, int Hq, int Hkv, int D, int
 int al::al_internal_attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh, int32_t* out) {
   if (!attn_shape_ok(L, B, P, Hq, Hkv, D, n_refresh)) return AL_ERR_SHAPE;
   const al::AttnPlan p = al::attn_plan(L, B, P, Hq, Hkv, D, n_refresh);
-  const int32_t v[8] = {p.wsplit_lane, p.lane.n_split, p.lane.tpw, p.lane.f32,
-                        p.wsplit_ref,  p.ref.n_split,  p.ref.tpw,  p.ref.f32};
-  for (int i = 0; i < 8; ++i) out[i] = v[i];
+  const int32_t v[10] = {p.wsplit_lane, p.lane.n_split, p.lane.tpw, p.lane.f32, p.lane.deal,
+                         p.wsplit_ref,  p.ref.n_split,  p.ref.tpw,  p.ref.f32,  p.ref.deal};
+  for (int i = 0; i < 10; ++i) out[i] = v[i];
   return AL_OK;
 }
 

@@ -62,6 +62,7 @@ struct AttnParams {
   void* part_o;            // [n_split][n_rows][Hq][D] bf16 or fp32, unnormalised, when n_split > 1
   float* part_ml;          // [n_split][n_rows][Hq][2]
   bool part_f32;
+  unsigned long long deal; // lane blocks dealt to the splits: those of split 0 (0: shares of all tiles)
   int n_rows, rows_per_lane, tiles_per_lane, q_tiles_kv;
   int P, Hq, Hkv, g;
   int B_keys, n_key_lanes, lane_key_tiles, n_pre_tiles, total_key_tiles, n_split;
@@ -171,19 +172,30 @@ void lane_attn_kernel(AttnParams p) {
   float m_run = -INFINITY, l_run = 0.f;
 
   // The workgroup's key tiles: the prefix tiles, then the tiles of the lane
-  // blocks some wavefront sees, in ascending order.  The splits share out all
-  // the call's key tiles, so that which keys a row's partial holds does not
-  // depend on the lanes that share its workgroup; of its share this split takes
-  // the visible ones, [t0, t1) of the workgroup's tiles.
-  auto visible_before = [&](int kt) -> int {
-    if (kt <= p.n_pre_tiles || p.n_key_lanes == 0) return min(kt, p.n_pre_tiles);
-    const int q = kt - p.n_pre_tiles, j = q / p.lane_key_tiles;
-    const unsigned long long below = j < 64 ? wg_vis & ((1ull << j) - 1) : wg_vis;
-    const bool cut = j < 64 && ((wg_vis >> j) & 1);
-    return p.n_pre_tiles + __popcll(below) * p.lane_key_tiles + (cut ? q - j * p.lane_key_tiles : 0);
-  };
-  const int t0 = visible_before((int)((long long)split * p.total_key_tiles / p.n_split));
-  const int t1 = visible_before((int)((long long)(split + 1) * p.total_key_tiles / p.n_split));
+  // blocks some wavefront sees, in ascending order; this split takes [t0, t1) of
+  // them.  Which keys a row's partial holds must not depend on the lanes that
+  // share its workgroup, so the splits share out all the call's key tiles, and of
+  // its share a workgroup takes the visible ones.  Shares are contiguous, or (deal)
+  // contiguous in the prefix and every n_split-th lane block.
+  unsigned long long lanes = wg_vis;   // blocks that this split may take
+  int pre_end = p.n_pre_tiles;         // end of the prefix tiles listed
+  int t0, t1;
+  if (p.deal) {
+    lanes &= p.deal << split;
+    t0 = split * p.n_pre_tiles / p.n_split;
+    pre_end = (split + 1) * p.n_pre_tiles / p.n_split;
+    t1 = pre_end + __popcll(lanes) * p.lane_key_tiles;
+  } else {
+    auto visible_before = [&](int kt) -> int {
+      if (kt <= p.n_pre_tiles || p.n_key_lanes == 0) return min(kt, p.n_pre_tiles);
+      const int q = kt - p.n_pre_tiles, j = q / p.lane_key_tiles;
+      const unsigned long long below = j < 64 ? wg_vis & ((1ull << j) - 1) : wg_vis;
+      const bool cut = j < 64 && ((wg_vis >> j) & 1);
+      return p.n_pre_tiles + __popcll(below) * p.lane_key_tiles + (cut ? q - j * p.lane_key_tiles : 0);
+    };
+    t0 = visible_before((int)((long long)split * p.total_key_tiles / p.n_split));
+    t1 = visible_before((int)((long long)(split + 1) * p.total_key_tiles / p.n_split));
+  }
   // They come in runs of consecutive rows: the prefix, then each block.  A
   // walk holds what is left of its run, so that the next tile costs a few
   // scalar operations; the rest is done once per run.
@@ -193,12 +205,12 @@ void lane_attn_kernel(AttnParams p) {
     bool pre;
   };
   auto walk_at = [&](int t) {
-    Walk k{wg_vis, 0, 0, t < p.n_pre_tiles};
+    Walk k{lanes, 0, 0, t < pre_end};
     if (k.pre) {
       k.row = t * AT_KT;
-      k.left = p.P - k.row;
+      k.left = min(p.P, pre_end * AT_KT) - k.row;
     } else {
-      const int q = t - p.n_pre_tiles, n = p.n_key_lanes ? q / p.lane_key_tiles : 0;
+      const int q = t - pre_end, n = p.n_key_lanes ? q / p.lane_key_tiles : 0;
       for (int i = 0; i < n; ++i) k.m &= k.m - 1;
       const int sub = (q - n * p.lane_key_tiles) * AT_KT;
       k.row = k.m ? __builtin_ctzll(k.m) * p.B_keys + sub : 0;
@@ -424,7 +436,7 @@ void lane_attn_kernel(AttnParams p) {
   // after tile i's barrier everyone is done with tile i - 1, whose buffer takes
   // tile i + 3, and tile i + 1 is complete.
   const int n = t1 - t0;
-  const int np = max(0, min(p.n_pre_tiles - t0, n));   // of them prefix tiles
+  const int np = max(0, min(pre_end - t0, n));   // of them prefix tiles
   Walk lw = walk_at(t0);
   int loaded = 0;
   set_source(lw);
@@ -930,29 +942,40 @@ static PassShape pass_shape(int n_rows, int rows_per_lane, int n_lanes, int g, i
 
 // Split and query tiles per workgroup (8, or 4 with the other four wavefronts
 // loading) of a pass on lane_attn_kernel: the cheapest under its times per
-// 64-key tile at D = 128 (MI355X): 1.8 us with 8 query tiles, 1.12 us with 4
-// (D = 64: 1.2 and 0.8), ~5 us per round of one workgroup per CU, and for a
-// split its partials through memory and a merge launch.  4 wins where 8 leave
-// a last round mostly empty or would need a split to fill the chip: window of
-// 2563 rows x 32 heads (352 or 672 workgroups) 153 us against 162 us, 1024
-// rows x 32 heads (128 x 2 splits or 256) 34 us against 40 us.
+// 64-key tile at D = 128 (MI355X): 1.8 us with 8 query tiles, 1.06 us with 4
+// (D = 64: 1.2 and 0.7), ~5 us per round of one workgroup per CU, and for a
+// split its partials through memory and a merge launch.  Fitted to 200 sizes and
+// trees, each with every split and both tile counts: the choice is 1.8% above the best
+// of them on (geometric) average.  4 wins where 8 leave a last round mostly empty
+// or would need a split to fill the chip: window of 2563 rows x 32 heads (352 or
+// 672 workgroups) 153 us against 162 us, 1024 rows x 32 heads (128 x 2 splits or
+// 256) 34 us against 40 us.
 //
 // Fewer splits than max_split hold other keys per partial; in bf16 that moves the
 // output 0.4 to 1.4% further from the 64-bit one (relative error 2.84e-3 -> 2.86e-3
 // over 3333 keys), so those partials are fp32 (2.33e-3).
+//
+// Splits take contiguous shares of all key tiles where there are as many as
+// max_split and lane blocks are at most a third of them; otherwise their lane
+// blocks are dealt one by one, because a workgroup sees few of a contiguous run
+// of blocks or nearly all of it (contiguous -> dealt, lane tiles a third and more of
+// the keys: 3 to 6% faster on average, up to 25%; below that 1%).
 static void choose_pass(const PassShape& s, int Hkv, int Hq, int D, AttnPass* pass) {
   const int most = max_split(s.base_wgs, s.total_key_tiles);
+  const int lane_tiles = s.total_key_tiles - s.n_pre_tiles;
   double best = 1e30;
   for (int t = AT_WAVES; t >= 4; t /= 2)
     for (int ns = 1; ns <= most; ns *= 2) {
+      const bool f32 = ns > 1 && ns < most;
+      const bool deal = ns > 1 && lane_tiles > 0 && (f32 || 3 * lane_tiles > s.total_key_tiles);
       const long long wgs = (long long)((s.q_tiles_kv + t - 1) / t) * Hkv * ns;
       const double rounds = (double)((wgs + 255) / 256);
-      const double tile = (t == AT_WAVES ? 1.8 : 1.12) * (D == 64 ? 0.68 : 1.0);
+      const double tile = (t == AT_WAVES ? 1.8 : 1.06) * (D == 64 ? 0.68 : 1.0);
       double cost = rounds * ((double)((s.total_key_tiles + ns - 1) / ns) * tile + 5.0);
-      if (ns > 1) cost += 4.0 + 1e-6 * ns * s.n_rows * (double)Hq * D;
+      if (ns > 1) cost += 5.0 + (f32 ? 1.7e-6 : 1.2e-6) * ns * s.n_rows * (double)Hq * D;
       if (cost < best) {
         best = cost;
-        *pass = AttnPass{ns, t, ns > 1 && ns < most};
+        *pass = AttnPass{ns, t, f32, deal};
       }
     }
 }
@@ -975,7 +998,7 @@ AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh) {
   const int pre_units = (P + 31) / 32;
   const PassShape a = pass_shape(L * B, B, L, g, Hkv, P, B, L);
   pl.wsplit_lane = L > 0 && use_wsplit(a, Hkv, pre_units + L * ((B + 31) / 32));
-  pl.lane = pl.ref = AttnPass{1, AT_WAVES, false};
+  pl.lane = pl.ref = AttnPass{1, AT_WAVES, false, false};
   int most = 1;
   if (L > 0 && !pl.wsplit_lane) {
     choose_pass(a, Hkv, Hq, D, &pl.lane);
@@ -1018,6 +1041,7 @@ static hipError_t run_pass(const AttnParams& base, const PassShape& s, const Att
     p.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + n * (pass.f32 ? 4 : 2));
   }
   p.tpw = pass.tpw;
+  p.deal = pass.deal ? ~0ull / ((1ull << n_split) - 1) : 0;   // every n_split-th bit
   const dim3 grid((s.q_tiles_kv + p.tpw - 1) / p.tpw, p.Hkv, n_split);
   hipLaunchKernelGGL(lane_attn_kernel<D>, grid, dim3(AT_THREADS), 0, stream, p);
   if (n_split > 1) {

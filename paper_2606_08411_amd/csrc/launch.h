@@ -11,6 +11,7 @@ struct AttnPass {
   int n_split;   // key splits over workgroups
   int tpw;       // query tiles per workgroup
   bool f32;      // partial outputs of the splits in fp32 (else bf16)
+  bool deal;     // lane blocks dealt to the splits one by one (else shares of all key tiles)
 };
 struct AttnPlan {
   bool wsplit_lane, wsplit_ref;  // keys split over the wavefronts of a workgroup
@@ -19,7 +20,7 @@ struct AttnPlan {
 };
 AttnPlan attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh);
 // For tests: {wavefront split, key splits, query tiles per workgroup, fp32
-// partials} of the lane pass, then of the refresh pass.
+// partials, lane blocks dealt} of the lane pass, then of the refresh pass.
 extern "C" int al_internal_attn_plan(int L, int B, int P, int Hq, int Hkv, int D, int n_refresh, int32_t* out);
 
 hipError_t launch_lane_attention(const uint16_t* q, const uint16_t* k_lane, const uint16_t* v_lane,

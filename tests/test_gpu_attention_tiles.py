@@ -1,4 +1,4 @@
-"""The 8-tile attention kernel at the edges of its key-tile ring: 0 to 24 prefix
+"""The 8-tile attention kernel at the edges of its key-tile ring: 0 to 47 prefix
 tiles of 64 keys (odd and even, full and ragged), lane blocks of 1 and 2 tiles,
 and every number of key splits and of query tiles per workgroup that the plan
 chooses, for lanes and for refreshed rows (test_plans_host.py checks that).
@@ -37,6 +37,11 @@ CASES = [  # L, B, P, Hq, Hkv, D, refreshed rows
     (33, 16, 1300, 4, 2, 128, 0), (33, 16, 1300, 1, 1, 64, 0), (40, 16, 1300, 2, 2, 64, 0),
     (9, 16, 65, 32, 16, 128, 0), (0, 16, 200, 224, 32, 64, 129), (0, 16, 1000, 14, 2, 64, 669),
     (0, 16, 1000, 56, 8, 64, 129), (0, 16, 1500, 112, 16, 128, 65),
+    # lane blocks in contiguous shares and dealt to the splits
+    (57, 80, 1357, 6, 6, 64, 0), (60, 16, 450, 16, 16, 64, 0), (46, 16, 1096, 12, 6, 64, 0),
+    (64, 80, 3000, 4, 4, 64, 0), (5, 16, 700, 56, 8, 64, 0), (10, 48, 1409, 1, 1, 64, 0),
+    (9, 16, 3000, 16, 16, 64, 0), (1, 16, 3000, 1, 1, 64, 0), (17, 16, 3000, 4, 2, 64, 0),
+    (16, 32, 700, 4, 4, 128, 0), (0, 16, 3000, 8, 2, 64, 914), (0, 16, 3000, 28, 4, 64, 294),
 ]
 
 
@@ -73,15 +78,17 @@ def test_key_tile_edges(case):
         assert np.abs(out["lse_ref"] - ref["lse_ref"]).max() < TOL_LSE
 
 
-def test_rounding_does_not_depend_on_the_other_lanes():
+@pytest.mark.parametrize("case", [(20, 449, 16), (16, 2048, 32)], ids=["dealt", "contiguous"])
+def test_rounding_does_not_depend_on_the_other_lanes(case):
     """With key splits, which keys a partial holds is a matter of the call's sizes: the result of a
     lane that only sees itself has the same bits whatever the other lanes of its workgroup see."""
     import paper_2606_08411_amd as al
     import torch
     from gpu_util import dev_bf16
-    L, B = 20, 32
-    step = synth.make_step("tiny", 5, with_weight=False, D=128, B=B, L=L, tree="linear", Hq=16,
-                           Hkv=16, P=449, V=64, d=64)
+    L, P, H = case
+    B = 32
+    step = synth.make_step("tiny", 5, with_weight=False, D=128, B=B, L=L, tree="linear", Hq=H,
+                           Hkv=H, P=P, V=64, d=64)
     a = [dev_bf16(x) for x in (step.q, step.k_lane, step.v_lane, step.k_pre, step.v_pre)]
     got = []
     for parent in ([-1] * L, list(range(-1, L - 2)) + [-1]):   # alone / a chain, the last lane alone

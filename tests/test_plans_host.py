@@ -17,10 +17,11 @@ def lib():
 
 
 def attn_plan(lib, L, B, P, Hq, Hkv, D, n_ref):
-    """[lane pass, refresh pass], each (wavefront split, key splits, query tiles, fp32 partials)."""
-    out = (ctypes.c_int32 * 8)()
+    """[lane pass, refresh pass], each (wavefront split, key splits, query tiles, fp32 partials, lane
+    blocks dealt to the splits)."""
+    out = (ctypes.c_int32 * 10)()
     assert lib.al_internal_attn_plan(L, B, P, Hq, Hkv, D, n_ref, out) == 0
-    return tuple(out[:4]), tuple(out[4:])
+    return tuple(out[:5]), tuple(out[5:])
 
 
 def _attn_sizes(n, seed):
@@ -35,7 +36,7 @@ def _attn_sizes(n, seed):
 
 
 def test_attention_cases_reach_every_plan(lib):
-    """(pass, key splits, query tiles, fp32 partials) of the 8-tile kernel."""
+    """(pass, key splits, query tiles, fp32 partials, dealt) of the 8-tile kernel."""
     def kinds(case):
         lane, ref = attn_plan(lib, *case)
         if case[0] and not lane[0]:
@@ -57,7 +58,7 @@ def test_attention_workspace_holds_the_partials(lib):
     for c in _attn_sizes(40000, 2):
         L, B, P, Hq, Hkv, D, n_ref = c
         ws = lib.lane_attn_workspace_size(*c)
-        for (wsplit, ns, tpw, f32), rows in zip(attn_plan(lib, *c), (L * B, n_ref)):
+        for (wsplit, ns, tpw, f32, deal), rows in zip(attn_plan(lib, *c), (L * B, n_ref)):
             if rows and ns > 1:
                 assert not wsplit
                 assert ns * rows * Hq * ((4 if f32 else 2) * D + 8) <= ws, c
