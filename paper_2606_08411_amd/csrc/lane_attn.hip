@@ -180,10 +180,12 @@ void lane_attn_kernel(AttnParams p) {
   unsigned long long lanes = wg_vis;   // blocks that this split may take
   int pre_end = p.n_pre_tiles;         // end of the prefix tiles listed
   int t0, t1;
+  const int split_log2 = __builtin_ctz(p.n_split);   // a power of two: no 64-bit division
+  auto share = [&](int i, int n) -> int { return (int)((long long)i * n >> split_log2); };
   if (p.deal) {
     lanes &= p.deal << split;
-    t0 = split * p.n_pre_tiles / p.n_split;
-    pre_end = (split + 1) * p.n_pre_tiles / p.n_split;
+    t0 = share(split, p.n_pre_tiles);
+    pre_end = share(split + 1, p.n_pre_tiles);
     t1 = pre_end + __popcll(lanes) * p.lane_key_tiles;
   } else {
     auto visible_before = [&](int kt) -> int {
@@ -193,8 +195,8 @@ void lane_attn_kernel(AttnParams p) {
       const bool cut = j < 64 && ((wg_vis >> j) & 1);
       return p.n_pre_tiles + __popcll(below) * p.lane_key_tiles + (cut ? q - j * p.lane_key_tiles : 0);
     };
-    t0 = visible_before((int)((long long)split * p.total_key_tiles / p.n_split));
-    t1 = visible_before((int)((long long)(split + 1) * p.total_key_tiles / p.n_split));
+    t0 = visible_before(share(split, p.total_key_tiles));
+    t1 = visible_before(share(split + 1, p.total_key_tiles));
   }
   // They come in runs of consecutive rows: the prefix, then each block.  A
   // walk holds what is left of its run, so that the next tile costs a few
